@@ -341,7 +341,7 @@ struct Detect2 {
 };
 
 // Detection tile rows and slab depth picked by ftk_autotune_cp2d, per (kind, nx, ny): consulted when the options
-// leave them at 0.  Without an entry: 16 rows, 16 steps (within a few per cent of the best on the workloads here).
+// leave them at 0.  Without an entry the rule of tuned_tiles2 below decides.
 struct TuneKey {
   int kind;
   long long nx, ny;
@@ -371,8 +371,35 @@ static void tune_store(int kind, long long nx, long long ny, int ty, int tt) {
   g_tune.push_back({TuneKey{kind, nx, ny}, {ty, tt}});
 }
 
+// Steps per slab for a kernel whose work units march `per_step` tiles through time: a slab of tt steps costs about
+// tt + extra plane passes, one after another, and the chip runs `resident` of them side by side before they slow each
+// other down.  The depth (at most `most`, slabs of even length) with the least (tt + extra) max(1, units / resident):
+// long slabs once the tiles of a step fill the chip, short ones when they would leave it idle (64 x 64 x 10 has eight
+// tiles a step).
+static int slab_steps(long long per_step, long long nt, int extra, long long resident, int most) {
+  int best = 1;
+  double best_cost = 1e300;
+  for (int tt = 1; tt <= most && tt <= nt; ++tt) {
+    const long long slabs = (nt + tt - 1) / tt;
+    const int even = (int)((nt + slabs - 1) / slabs);
+    const double load = (double)per_step * (double)slabs / (double)resident;
+    const double cost = (even + extra) * (load > 1.0 ? load : 1.0);
+    if (cost <= best_cost) {  // equal cost: the longer slab
+      best_cost = cost;
+      best = even;
+    }
+  }
+  return best;
+}
+
+// Detection: wavefronts of 64 x 8 anchors; two of them per SIMD keep it issuing.  Workgroups of four wavefronts share
+// halo rows in the CU's cache; when there is less than a wavefront per SIMD, single ones spread over more CUs.
+constexpr long long kDetResident = 2048;
+
 static void tuned_tiles2(const ftk_options& o, int kind, long long nx, long long ny, int nt, int* ty, int* tt) {
-  int dty = 16, dtt = 16;
+  const long long waves = ((nx + 63) / 64) * ((ny + kDetectRows - 1) / kDetectRows);
+  int dtt = slab_steps(waves, nt, 1, kDetResident, 16);
+  int dty = waves * ((nt + dtt - 1) / dtt) < 4 * kDetResident ? 8 : 32;
   tune_lookup(kind, nx, ny, &dty, &dtt);
   *ty = o.tile_y ? o.tile_y : dty;
   *tt = o.slab_depth ? o.slab_depth : dtt;
@@ -496,28 +523,16 @@ ftk_status track2d_core(const float* field, ftk_field_kind kind, int64_t nx, int
   int ty, tt;
   tuned_tiles2(o, g.kind, nx, ny, g.nt, &ty, &tt);
   Ctl h;
-  bool wide = false;
   Phases ph;
   ph.init(o.profile != 0, s);
   ph.mark(0);
-  HIP_TRY(launch_detect2d(g, ty, tt, false, masks, seg_cnt, &dctl->status, s));
+  HIP_TRY(launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));
   ph.mark(1);
   HIP_TRY(launch_scan(seg_cnt, seg_off, nseg, &dctl->total, scan_tmp, s));
   ph.mark(2);
   ftk_status st = read_ctl(&h, dctl, s);
   if (st) return st;
-  if (h.status & ST_NONFINITE) return decode_status(h.status);
-  if (h.status & ST_WIDE) {
-    wide = true;
-    HIP_TRY(clear_ctl(dctl, s));
-    ph.mark(0);
-    HIP_TRY(launch_detect2d(g, ty, tt, true, masks, seg_cnt, &dctl->status, s));
-    ph.mark(1);
-    HIP_TRY(launch_scan(seg_cnt, seg_off, nseg, &dctl->total, scan_tmp, s));
-    ph.mark(2);
-    st = read_ctl(&h, dctl, s);
-    if (st) return st;
-  }
+  const bool wide = (h.status & ST_WIDE) != 0;
   st = decode_status(h.status);
   if (st) return st;
   const long long nh = h.total;
@@ -814,14 +829,17 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
                                 ftk_cp_result* outs) {
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
-  constexpr int TYD = 16, TYE = 8;
-  // slab depth: the option, else the tuned one of the series with the most vertices, else 16 (rows fixed at 16)
+  constexpr int TYD = kDetectRows, TYE = 8;  // rows of a detection wavefront, of an emission tile
+  // slab depth: the option, else the tuned one of the series with the most vertices, else the rule for all tiles
   int ttd = o.slab_depth;
   if (!ttd) {
     int big = 0;
-    for (int i = 1; i < nser; ++i)
+    long long waves = 0;
+    for (int i = 0; i < nser; ++i) {
       if (nx[i] * ny[i] * nt[i] > nx[big] * ny[big] * nt[big]) big = i;
-    int tty = 16, ttt = 16;
+      waves += ((nx[i] + 63) / 64) * ((ny[i] + TYD - 1) / TYD);
+    }
+    int tty, ttt = slab_steps(waves, nt[big], 1, kDetResident, 16);
     tune_lookup((int)kind, nx[big], ny[big], &tty, &ttt);
     ttd = ttt;
   }
@@ -884,27 +902,20 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
   HIP_TRY(hipMemcpyAsync(dseg_start, seg_start.data(), sizeof(long long) * nser, hipMemcpyHostToDevice, s));
   Phases ph;
   ph.init(o.profile != 0, s);
-  bool wide = false;
   Ctl h;
   std::vector<long long> bases(nser + 1);
-  for (int pass = 0; pass < 2; ++pass) {
-    ph.mark(0);
-    HIP_TRY(launch_detect2d_batched(dser, dpre, nser, pre_d[nser], ttd, wide, dctr, &dctl->status, s));
-    ph.mark(1);
-    HIP_TRY(launch_scan(seg_cnt, seg_off, Stot, &dctl->total, scan_tmp, s));
-    gather_bases<<<(nser + 256) / 256, 256, 0, s>>>(seg_off, dseg_start, nser, &dctl->total, dbases);
-    HIP_TRY(hipGetLastError());
-    ph.mark(2);
-    HIP_TRY(hipMemcpyAsync(bases.data(), dbases, sizeof(long long) * (nser + 1), hipMemcpyDeviceToHost, s));
-    ftk_status st = read_ctl(&h, dctl, s);
-    if (st) return st;
-    if (h.status & ST_NONFINITE) return decode_status(h.status);
-    if (!(h.status & ST_WIDE) || wide) break;
-    wide = true;
-    HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
-    HIP_TRY(hipMemsetAsync(dctr, 0, sizeof(int) * 4, s));
-  }
-  ftk_status st = decode_status(h.status);
+  ph.mark(0);
+  HIP_TRY(launch_detect2d_batched(dser, dpre, nser, pre_d[nser], ttd, (int)kind, dctr, &dctl->status, s));
+  ph.mark(1);
+  HIP_TRY(launch_scan(seg_cnt, seg_off, Stot, &dctl->total, scan_tmp, s));
+  gather_bases<<<(nser + 256) / 256, 256, 0, s>>>(seg_off, dseg_start, nser, &dctl->total, dbases);
+  HIP_TRY(hipGetLastError());
+  ph.mark(2);
+  HIP_TRY(hipMemcpyAsync(bases.data(), dbases, sizeof(long long) * (nser + 1), hipMemcpyDeviceToHost, s));
+  ftk_status st = read_ctl(&h, dctl, s);
+  if (st) return st;
+  const bool wide = (h.status & ST_WIDE) != 0;
+  st = decode_status(h.status);
   if (st) return st;
   const long long total = h.total;
   if (total > 0xFFFFFFFELL) return fail(FTK_ERR_CAPACITY, "%lld punctured simplices in the batch exceed 2^32 - 2", total);
@@ -1170,21 +1181,15 @@ static ftk_status tracker_detect(ftk_tracker* h, int p, int nt) {
   const int slot = p % 3;
   int* cnt = h->cring + (size_t)slot * h->nseg_plane;
   long long* off = h->oring + (size_t)slot * h->nseg_plane;
-  int ty = h->o.tile_y ? h->o.tile_y : 16;
-  for (int pass = 0; pass < 2; ++pass) {
-    const bool wide = pass == 1;
-    HIP_TRY(hipMemsetAsync(&dctl->dstatus, 0, sizeof(unsigned), h->s));
-    HIP_TRY(launch_detect2d(g, ty, 1, wide, h->mring, h->cring, &dctl->dstatus, h->s));
-    unsigned st = 0;
-    HIP_TRY(hipMemcpyAsync(&st, &dctl->dstatus, sizeof(unsigned), hipMemcpyDeviceToHost, h->s));
-    HIP_TRY(hipStreamSynchronize(h->s));
-    if (st & ST_NONFINITE) return decode_status(st);
-    if (st & ST_RANGE) return decode_status(st);
-    if (!(st & ST_WIDE)) {
-      h->plane_wide[slot] = wide ? 1 : 0;
-      break;
-    }
-  }
+  const long long waves = ((h->nx + 63) / 64) * ((h->ny + kDetectRows - 1) / kDetectRows);
+  const int ty = h->o.tile_y ? h->o.tile_y : (waves < 4 * kDetResident ? 8 : 32);
+  HIP_TRY(hipMemsetAsync(&dctl->dstatus, 0, sizeof(unsigned), h->s));
+  HIP_TRY(launch_detect2d(g, ty, 1, h->mring, h->cring, &dctl->dstatus, h->s));
+  unsigned st = 0;
+  HIP_TRY(hipMemcpyAsync(&st, &dctl->dstatus, sizeof(unsigned), hipMemcpyDeviceToHost, h->s));
+  HIP_TRY(hipStreamSynchronize(h->s));
+  if (st & (ST_NONFINITE | ST_RANGE)) return decode_status(st);
+  h->plane_wide[slot] = (st & ST_WIDE) ? 1 : 0;
   HIP_TRY(launch_scan(cnt, off, h->nseg_plane, h->dplane, h->scan_tmp, h->s));
   add_plane_base<<<(unsigned)((h->nseg_plane + 255) / 256), 256, 0, h->s>>>(off, h->nseg_plane, &dctl->total);
   bump_running<<<1, 1, 0, h->s>>>(&dctl->total, h->dplane);
@@ -2328,9 +2333,9 @@ extern "C" ftk_status ftk_autotune_cp2d(const float* field, ftk_field_kind kind,
     for (int b = 0; b < 3; ++b) {
       const int ty = rows[a], tt = slabs[b] < nt ? slabs[b] : (int)nt;
       if (b > 0 && slabs[b - 1] >= nt) continue;  // same clamped depth as the previous candidate
-      HIP_TRY(ftk::launch_detect2d(g, ty, tt, false, masks, seg_cnt, &dctl->status, s));  // warm-up
+      HIP_TRY(ftk::launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));  // warm-up
       ph.mark(0);
-      for (int r = 0; r < 2; ++r) HIP_TRY(ftk::launch_detect2d(g, ty, tt, false, masks, seg_cnt, &dctl->status, s));
+      for (int r = 0; r < 2; ++r) HIP_TRY(ftk::launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));
       ph.mark(1);
       HIP_TRY(hipStreamSynchronize(s));
       const float ms = ph.ms(0, 1);

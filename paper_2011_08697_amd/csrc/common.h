@@ -84,44 +84,6 @@ __device__ __forceinline__ float diff3(float lo, float mid, float hi, int i, int
 __device__ __forceinline__ float quant(float v, float scale) { return rintf(v * scale); }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Simulation of Simplicity for the 2x2 determinant of columns A (lower vertex index) and B.  Each entry (j, k)
-// carries eps^(2^(2k+j)); the perturbed determinant is
-//   (A0 B1 - A1 B0) + B1 e^1 - B0 e^2 - A1 e^4 - e^6 + A0 e^8 + e^9,
-// so its sign is that of the first nonzero of (det, B1, -B0, -A1, -1).  Returned as a bit: 1 for positive.
-// ---------------------------------------------------------------------------------------------------------------
-template <typename Q>
-__device__ __forceinline__ unsigned sos2_positive(Q a0, Q a1, Q b0, Q b1);
-
-// Narrow path: components are integers below 2^24 carried in binary32 (exactly).  Both products are integers below
-// 2^48 and their difference is below 2^49, so the binary64 evaluation below is the exact integer determinant.
-template <>
-__device__ __forceinline__ unsigned sos2_positive<float>(float a0, float a1, float b0, float b1) {
-  const double p = (double)a1 * (double)b0;
-  const double d = __builtin_fma((double)a0, (double)b1, -p);
-  const unsigned r = d > 0.0;
-  const unsigned seq = (b1 != 0.0f) ? (b1 > 0.0f) : ((b0 != 0.0f) ? (b0 < 0.0f) : ((a1 != 0.0f) ? (a1 < 0.0f) : 0u));
-  return d != 0.0 ? r : seq;
-}
-
-// The same on values already converted to binary64 (exact integers below 2^24).
-__device__ __forceinline__ unsigned sos2_positive_d(double a0, double a1, double b0, double b1) {
-  const double d = __builtin_fma(a0, b1, -(a1 * b0));
-  const unsigned seq = (b1 != 0.0) ? (b1 > 0.0) : ((b0 != 0.0) ? (b0 < 0.0) : ((a1 != 0.0) ? (a1 < 0.0) : 0u));
-  return d != 0.0 ? (unsigned)(d > 0.0) : seq;
-}
-
-// Wide path: 64-bit components below 2^62, 128-bit products.
-template <>
-__device__ __forceinline__ unsigned sos2_positive<long long>(long long a0, long long a1, long long b0, long long b1) {
-  i128 d = (i128)a0 * b1 - (i128)a1 * b0;
-  if (d != 0) return d > 0;
-  if (b1 != 0) return b1 > 0;
-  if (b0 != 0) return b0 < 0;
-  if (a1 != 0) return a1 < 0;
-  return 0u;
-}
-
-// ---------------------------------------------------------------------------------------------------------------
 // Classification (Sec. 4.1): types from the spatial Jacobian interpolated at the zero, J_c = sum mu_i J(v_i).
 // Reference semantics are binary64 in a fixed order; the FP32 evaluation is accepted only when every sign it
 // decides is certified: |value32| > E32 + E64, where E32 and E64 bound the distance of the binary32 and binary64

@@ -8,10 +8,10 @@
 // shared by the triangles through LDS.
 //
 // Kernels:
-//   detect2d  -- time-marching slab kernel over a 64 x TY tile (TX = one wavefront): loads the field plane with a
-//                2-cell halo into LDS, forms the gradient (scalar input), quantises, evaluates the 7 edge signs of
-//                every vertex of the tile (+1 halo) and the 12 triangle tests of every anchor; writes a 12-bit
-//                puncture mask per vertex and the hit count of every 64-vertex row segment.
+//   detect2d  -- one wavefront per 64 x 8 tile, marching through a slab of steps with the vectors of two planes in
+//                registers: gradient (scalar input), quantisation, the 7 edge signs of every vertex as wave masks and
+//                the 12 triangle tests of every anchor on them; writes a 12-bit puncture mask per vertex and the hit
+//                count of every 64-vertex row segment.
 //   emit2d    -- one wavefront per row segment: prefix sums give each hit its output index (face ids come out
 //                sorted); computes the sublocation (Eq. 2) from the exact cofactors, the Jacobian type (FP32 with
 //                certified FP64 fallback), and the union-find links of the hit's two tetrahedra (Alg. 1 pass 2).
@@ -25,61 +25,7 @@ namespace {
 constexpr int TX = 64;
 constexpr int kEmitTT = 16;  // steps per emission workgroup
 
-// triangle types using each axis (validity masks at the last index of an axis)
-constexpr unsigned kUseX = (unsigned)types_using_axis(kTri2, 1);
-constexpr unsigned kUseY = (unsigned)types_using_axis(kTri2, 2);
-constexpr unsigned kUseT = (unsigned)types_using_axis(kTri2, 4);
-
-// Quantised components: the narrow path keeps integers below 2^24 in binary32 (exact, and every determinant and
-// cofactor of the path stays exact in binary64); the wide path keeps 64-bit integers below 2^62.
-template <bool WIDE>
-struct QType;
-template <>
-struct QType<false> {
-  typedef float T;
-};
-template <>
-struct QType<true> {
-  typedef long long T;
-};
-
-constexpr float kNarrow2 = 16777216.0f;  // 2^24
-
-// Bit-gather tables for the 12 triangle tests: t[0][w] bit k = edge-word bit (M1 - 1) (edge v0 v1), t[1][w] bit k =
-// bit (M1|M2 - 1) (edge v0 v2), t[1 + n][w] bit k = bit (M2 - 1) for the types with M1 = n (edge v1 v2, read from
-// the word of the neighbour p + e(n)).
-struct Tri2Lut {
-  unsigned short t[8][128];
-};
-constexpr Tri2Lut build_tri2_lut() {
-  Tri2Lut r{};
-  for (int w = 0; w < 128; ++w)
-    for (int k = 0; k < 12; ++k) {
-      const int m1 = kTri2.m[k][0], m2 = kTri2.m[k][1];
-      if ((w >> (m1 - 1)) & 1) r.t[0][w] |= (unsigned short)(1u << k);
-      if ((w >> ((m1 | m2) - 1)) & 1) r.t[1][w] |= (unsigned short)(1u << k);
-      if ((w >> (m2 - 1)) & 1) r.t[1 + m1][w] |= (unsigned short)(1u << k);
-    }
-  return r;
-}
-constexpr Tri2Lut kTri2Lut = build_tri2_lut();
-
-template <bool WIDE>
-__device__ __forceinline__ typename QType<WIDE>::T to_q(float r, unsigned& st) {
-  if (!WIDE) {
-    if (!(fabsf(r) < kNarrow2)) {
-      st |= ST_WIDE;
-      return 0.0f;
-    }
-    return r;
-  } else {
-    if (!(fabsf(r) < 4611686018427387904.0f)) {
-      st |= ST_RANGE;
-      return 0;
-    }
-    return (long long)r;
-  }
-}
+constexpr float kNarrow2 = 16777216.0f;  // 2^24: cofactors and their sum stay exact in binary64 below it
 
 __device__ __forceinline__ int fpl(const Grid2& g, int t) { return g.f_ring ? t % g.f_ring : t; }
 __device__ __forceinline__ int mpl(const Grid2& g, int t) { return g.m_ring ? t % g.m_ring : t; }
@@ -88,273 +34,431 @@ __device__ __forceinline__ int mpl(const Grid2& g, int t) { return g.m_ring ? t 
 
 // ---------------------------------------------------------------------------------------------------------------
 // Pass 1: detection.
-// grid = (ceil(nx / 64), ceil(ny / TY), ceil(nt / TT)), block = 256.
+//
+// A wavefront owns a tile of 64 x 8 anchors (lane = x) and marches it through the steps of a slab, with no LDS and no
+// barrier: the quantised vectors of the planes t and t + 1 stay in registers (nine rows: the tile's and the one
+// above), the x + 1 neighbour of a lane comes from a whole-wave DPP shift, and the one column past lane 63 is held
+// lane-parallel (lane r + 1 = row r), so it costs one extra vector per plane and not one per row.  The field rows of
+// the plane after next are in flight while a step is evaluated.
+//
+// The sign of an edge determinant is decided in binary64: a quantised component is the rounding of a binary32 value,
+// so it has at most 24 significant bits at any magnitude, the product a1 b0 is exact and fma(a0, b1, -a1 b0) rounds
+// the exact difference once -- its sign, zero included, is the exact one over the whole accepted range (|q| < 2^62).
+// One variant therefore serves what the emission splits into a narrow and a 128-bit form.
+//
+// The sign of a determinant is the top bit of its high word, and the 12 triangle tests of an anchor are bit-parallel on
+// words that these bits are spread into (TriSpread).  (Wave masks of the signs in scalar registers, with the tests as
+// 64-bit scalar operations, were bound by scalar issue: 0.57 against 0.43 ms on 1024 x 1024 x 100.)
+//
+// Eight rows a wavefront need 160 registers (three wavefronts per SIMD); four rows run four wavefronts but load,
+// quantise and test more halo (0.49 against 0.43 ms), and eight rows held to 128 registers spill (0.76 ms).
+//
+// Measured against tiles of 64 x 16 staged in LDS with one workgroup barrier per pass: 1024 x 1024 x 100 scalar noise
+// 1.01 -> 0.43 ms, 4096 x 4096 x 50 vector 3.77 -> 2.25 ms, 1021 x 769 x 40 vector beyond 2^24 (then a narrow run and
+// a 128-bit one) 0.69 -> 0.13 ms, 64 x 64 x 10 scalar 84 -> 9 us.
+//
+// A step whose vectors carry a sign fact over the tile skips the edges and the tests: when one component is of one
+// strict sign at every vertex of both planes it keeps that sign under the symbolic perturbation (its entries move by
+// infinitesimals only), so the origin is outside every triangle; with every vector zero each edge determinant takes
+// the perturbation's last, negative term, so the three cofactor signs never agree.
+//
+// Bound: reading the field and writing the masks for sparse fields (8.4 GB at 3.7 TB/s on 4096 x 4096 x 50), VALU issue
+// (about 75 operations a row and step) otherwise.
 // ---------------------------------------------------------------------------------------------------------------
-template <int TY, bool WIDE>
-__device__ __forceinline__ void detect2d_tile(const Grid2& g, int TT, int bx, int by, int bz,
+namespace {
+
+constexpr int kDetRows = kDetectRows;      // anchor rows per wavefront
+static_assert(8 % kDetRows == 0, "workgroups of 8, 16 and 32 rows are whole wavefronts");
+constexpr int kDetVec = kDetRows + 1;      // rows of vectors
+constexpr int kDetRaw = kDetRows + 3;      // scalar field rows behind them
+
+typedef unsigned long long u64;
+
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// v of the next lane; lane 63 takes `past`
+__device__ __forceinline__ float from_next(float v, float past) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(__float_as_int(past), __float_as_int(v), 0x130, 0xf, 0xf, false));  // wave_shl:1
+}
+// v of the previous lane; lane 0 takes `before`
+__device__ __forceinline__ float from_prev(float v, float before) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(__float_as_int(before), __float_as_int(v), 0x138, 0xf, 0xf, false));  // wave_shr:1
+}
+// v of lane i - 1 / i + 1 within the first 16 lanes (lanes without a source keep their own)
+__device__ __forceinline__ float row_prev(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x111, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_next(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x101, 0xf, 0xf, false));
+}
+
+// Field values of one plane behind the vectors of a tile.  Scalar: rows y0-1 .. y0+9 and, lane i = row y0-1+i, the
+// columns x0-1, x0+63, x0+64, x0+65.  Vector: rows y0 .. y0+8 of both components and the column x0+64.
+template <bool VEC>
+struct DetRaw {
+  float r[VEC ? 2 * kDetVec : kDetRaw];
+  float h[VEC ? 2 : 4];
+};
+// Quantised vectors of one plane: q[row][component], the column x0+64 in h (lane r + 1 = row r).
+struct DetPlane {
+  float q[kDetVec][2];
+  float h[2];
+};
+
+// Simulation of Simplicity for the 2x2 determinant of the columns a (lower vertex index) and b.  Each entry (j, k)
+// carries eps^(2^(2k+j)); the perturbed determinant is
+//   (a0 b1 - a1 b0) + b1 e^1 - b0 e^2 - a1 e^4 - e^6 + a0 e^8 + e^9,
+// so its sign is that of the first nonzero of (det, b1, -b0, -a1, -1): edge_tie gives it for an exact zero,
+__device__ __forceinline__ double edge_det(double a0, double a1, double b0, double b1) {
+  return __builtin_fma(a0, b1, -(a1 * b0));
+}
+// as a full mask, ~0 for negative (on the high words, without branches; a shifted-out sign leaves 0 for +-0).
+__device__ __forceinline__ int edge_tie(double a1, double b0, double b1) {
+  const int ha1 = __double2hiint(a1), hb0 = __double2hiint(b0), hb1 = __double2hiint(b1);
+  int s = (ha1 << 1) != 0 ? ~ha1 : -1;
+  s = (hb0 << 1) != 0 ? ~hb0 : s;
+  s = (hb1 << 1) != 0 ? hb1 : s;
+  return s >> 31;
+}
+// ~0 for a negative determinant, else 0 (either for a zero, which the caller settles with edge_tie)
+__device__ __forceinline__ int edge_neg(double d) { return __double2hiint(d) >> 31; }
+// Smallest of z and the magnitudes of the high words of two determinants, read as binary32: zero iff one of the
+// determinants is zero (a nonzero one is an integer, whose high word is that of a value of at least one).
+__device__ __forceinline__ float zero_seen(float z, double d, double e) {
+  asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(z) : "v"(__double2hiint(d)), "v"(__double2hiint(e)));
+  return z;
+}
+
+// The 12 triangle tests of an anchor run bit-parallel on three words with one bit per triangle type (M1, M2): E0, E1,
+// E2 hold the sign of the edge opposite v0, v1, v2 -- the edges M2 of p + e(M1), M1|M2 of p and M1 of p.  The cofactor
+// signs +S, -S, +S agree iff E0 = E2 != E1.  Each edge sign (a full lane mask) is spread over the types it serves by
+// one and-or with a constant: fields of one word for E2 (bits 0-11) and E1 (bits 16-27) of the anchor's own edges, and
+// the E0 bits of the anchors below it in x, y and t.
+struct TriSpread {
+  unsigned own[8];   // by edge mask: E2 bits, E1 bits << 16
+  unsigned g[8];     // E0 bits at the anchor x - 1
+  unsigned h[8];     // E0 bits at the anchor y - 1
+  unsigned k[8];     // E0 bits at the anchor t - 1 (same x, y)
+  unsigned gt[8];    // E0 bits at x - 1, t - 1
+  unsigned ht[8];    // E0 bits at y - 1, t - 1
+  unsigned gxy[8];   // E0 bits at x - 1, y - 1
+};
+constexpr TriSpread build_tri_spread() {
+  TriSpread r{};
+  for (int ty = 0; ty < 12; ++ty) {
+    const int m1 = kTri2.m[ty][0], m2 = kTri2.m[ty][1];
+    r.own[m1] |= 1u << ty;
+    r.own[m1 | m2] |= 1u << (ty + 16);
+    unsigned* at = m1 == 1 ? r.g : (m1 == 2 ? r.h : (m1 == 3 ? r.gxy : (m1 == 4 ? r.k : (m1 == 5 ? r.gt : r.ht))));
+    at[m2] |= 1u << ty;
+  }
+  return r;
+}
+constexpr TriSpread kSpread = build_tri_spread();
+constexpr unsigned kGOwn = kSpread.g[2] | kSpread.g[4] | kSpread.g[6] | kSpread.gt[2];  // E0 bits from x + 1, same row
+constexpr unsigned kGXy = kSpread.gxy[4];                                                // from x + 1, y + 1
+static_assert((kGOwn & kGXy) == 0 && kSpread.gxy[4] != 0, "distinct E0 bits in the word passed along x");
+constexpr unsigned types_using(int axis) { return (unsigned)types_using_axis(kTri2, axis); }
+
+__device__ __forceinline__ unsigned spread(int neg, unsigned bits, unsigned acc) { return ((unsigned)neg & bits) | acc; }
+__device__ __forceinline__ unsigned from_next(unsigned v, unsigned past) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)past, (int)v, 0x130, 0xf, 0xf, false);  // wave_shl:1
+}
+
+}  // namespace
+
+template <bool VEC>
+__device__ __forceinline__ void detect2d_wave(const Grid2& g, int TT, int bx, int y0, int bz,
                                               uint16_t* __restrict__ masks, int* __restrict__ seg_cnt,
                                               unsigned* __restrict__ status) {
-  typedef typename QType<WIDE>::T Q;
-  constexpr int FW = TX + 4, FH = TY + 4;  // field plane + 2-cell halo (x0-1 .. x0+TX+2)
-  constexpr int QW = TX + 2, QH = TY + 2;  // quantised vectors (x0 .. x0+TX+1)
-  constexpr int EW = TX + 1, EH = TY + 1;  // edge words (x0 .. x0+TX)
-  __shared__ float fs[FH * FW];     // scalar input: the field plane being loaded
-  __shared__ Q qs[2][2][QH * QW];  // [plane parity][component]
-  __shared__ uint8_t ew[2][EH * EW];
-
-  const int tid = threadIdx.x;
-  const int x0 = bx * TX, y0 = by * TY;
+  const int lane = lane_id();
+  const int nx = g.nx, ny = g.ny, nt = g.nt;
+  const int x0 = bx * TX, gx = x0 + lane;
   const int t0 = g.t_begin + bz * TT;
   const int t1 = min(t0 + TT, g.t_end);
-  const int nx = g.nx, ny = g.ny, nt = g.nt;
   const long long plane = (long long)nx * ny;
-  unsigned st = 0;
-  unsigned facts = 0x1Fu;  // sign facts of the vectors quantised by this thread since the last plane_facts()
-  auto fact_bits = [](Q a, Q b) -> unsigned {
-    return (a > (Q)0 ? 1u : 0u) | (a < (Q)0 ? 2u : 0u) | (b > (Q)0 ? 4u : 0u) | (b < (Q)0 ? 8u : 0u) |
-           ((a == (Q)0 && b == (Q)0) ? 16u : 0u);
-  };
+  const unsigned xb = 4u * (unsigned)min(gx, nx - 1);  // byte offset in a row: 32-bit lane offsets to scalar addresses
+  const long long row_bytes = 4ll * nx;
+  // All loads use clamped (in-grid) addresses.  A clamped neighbour equals the value at the grid's edge, which turns
+  // the central difference into the one-sided one there; only its factor differs.
+  const float one = g.qscale, half = 0.5f * g.qscale;  // powers of two: exact factors
+  const int one_bits = __builtin_amdgcn_readfirstlane(__float_as_int(one));  // scalar: chosen per row
+  const int half_bits = __builtin_amdgcn_readfirstlane(__float_as_int(half));
+  const float sx = (gx == 0 || gx == nx - 1) ? one : half;
+  const float sxh = x0 + 64 == nx - 1 ? one : half;
+  const int hy = y0 - 1 + lane;  // grid row of this lane's part of the column past the tile
+  const float syh = (hy <= 0 || hy >= ny - 1) ? one : half;
+  const int hyc = min(max(y0 - 1 + min(lane, kDetRaw - 1), 0), ny - 1);
+  const u64 below = ~0ull >> (63 - min(63, nx - 1 - x0));            // lanes inside the grid
+  const u64 h_in = x0 + 64 < nx ? ((1ull << min(kDetVec, ny - y0)) - 1ull) << 1 : 0ull;
 
-  // Load plane t: scalar input into fs (FH x FW with halo); vector input straight into qs[par] (quantised).  The
-  // loads use clamped (in-grid) addresses and are issued back to back; cells outside the grid are zeroed after.
-  auto load_plane = [&](int t, int par) {
-    if (g.kind == 0) {
-      constexpr int NL = (FH * FW + 255) / 256;
-      const float* src = g.f + (long long)fpl(g, t) * plane;
-      float fv[NL];
-      bool in[NL];
+  // The tile's first row, opaque to the compiler: what is derived from it per row (addresses, row masks) is redone
+  // per step on the scalar unit and not held across steps, where it would not fit the scalar registers.
+  auto first_row = [&]() -> int {
+    int y = y0;
+    asm volatile("" : "+s"(y));
+    return y;
+  };
+  auto load = [&](int t, DetRaw<VEC>& w) {
+    const int y0 = first_row();
+    const float* P = g.f + (long long)fpl(g, t) * (VEC ? 2 * plane : plane);
+    constexpr int first = VEC ? 0 : -1;  // rows y0 - 1 (scalar) or y0 (vector) and up
+    const long long comp = plane * 4;
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        int e = tid + 256 * i;
-        asm volatile("" : "+v"(e));  // opaque: the index math is redone per plane, not held across steps
-        const int ly = e / FW, lx = e - ly * FW;
-        const int gx = x0 - 1 + lx, gy = y0 - 1 + ly;
-        in[i] = e < FH * FW && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-        fv[i] = src[(long long)min(max(gy, 0), ny - 1) * nx + min(max(gx, 0), nx - 1)];
+    for (int i = 0; i < (VEC ? kDetVec : kDetRaw); ++i) {
+      const char* row = (const char*)P + (long long)min(max(y0 + first + i, 0), ny - 1) * row_bytes;
+      if constexpr (VEC) {
+        w.r[2 * i] = *(const float*)(row + xb);
+        w.r[2 * i + 1] = *(const float*)(row + comp + xb);
+      } else {
+        w.r[i] = *(const float*)(row + xb);
       }
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int e = tid + 256 * i;
-        const float v = in[i] ? fv[i] : 0.0f;
-        if (in[i] && !isfinite(v)) st |= ST_NONFINITE;
-        if (e < FH * FW) fs[e] = v;
-      }
+    }
+    if constexpr (VEC) {
+      const long long o = (long long)hyc * nx + min(x0 + 64, nx - 1);
+      w.h[0] = P[o];
+      w.h[1] = P[o + plane];
     } else {
-      constexpr int NL = (QH * QW + 255) / 256;
-      const float* su = g.f + (long long)fpl(g, t) * 2 * plane;
-      const float* sv = su + plane;
-      float f0[NL], f1[NL];
-      bool in[NL];
+      const float* H = P + (long long)hyc * nx;
+      w.h[0] = H[max(x0 - 1, 0)];
+      w.h[1] = H[min(x0 + 63, nx - 1)];
+      w.h[2] = H[min(x0 + 64, nx - 1)];
+      w.h[3] = H[min(x0 + 65, nx - 1)];
+    }
+  };
+
+  unsigned st = 0;
+  float nonfinite = 0.0f;  // NaN once an infinity or NaN was loaded
+  // Quantised vectors of a loaded plane; returns its sign facts over the tile (bit 0 every x component > 0, bit 1
+  // every one < 0, bits 2 and 3 the y component, bit 4 every vector zero).
+  auto quantise = [&](const DetRaw<VEC>& w, DetPlane& p) -> unsigned {
+    const int y0 = first_row();
+    if constexpr (VEC) {
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        int e = tid + 256 * i;
-        asm volatile("" : "+v"(e));
-        const int ly = e / QW, lx = e - ly * QW;
-        const int gx = x0 + lx, gy = y0 + ly;
-        in[i] = e < QH * QW && gx < nx && gy < ny;
-        const long long k = (long long)min(gy, ny - 1) * nx + min(gx, nx - 1);
-        f0[i] = su[k];
-        f1[i] = sv[k];
-      }
+      for (int r = 0; r < kDetVec; ++r)
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int e = tid + 256 * i;
-        Q q0 = 0, q1 = 0;
-        if (in[i]) {
-          if (!isfinite(f0[i]) || !isfinite(f1[i])) st |= ST_NONFINITE;
-          q0 = to_q<WIDE>(quant(f0[i], g.qscale), st);
-          q1 = to_q<WIDE>(quant(f1[i], g.qscale), st);
-          facts &= fact_bits(q0, q1);
+        for (int c = 0; c < 2; ++c) {
+          nonfinite = __builtin_fmaf(w.r[2 * r + c], 0.0f, nonfinite);
+          p.q[r][c] = rintf(w.r[2 * r + c] * one);
         }
-        if (e < QH * QW) {
-          qs[par][0][e] = q0;
-          qs[par][1][e] = q1;
-        }
-      }
-    }
-  };
-
-  // Quantised gradient of plane (parity par) from fs (scalar input; vector input is quantised while loading).
-  auto quantise_plane = [&](int par) {
-    if (g.kind != 0) return;
-    for (int e = tid; e < QH * QW; e += 256) {
-      int ly = e / QW, lx = e - ly * QW;
-      int gx = x0 + lx, gy = y0 + ly;
-      Q q0 = 0, q1 = 0;
-      if (gx < nx && gy < ny) {
-        const float* r = &fs[(ly + 1) * FW + (lx + 1)];
-        const float v0 = diff3(r[-1], r[0], r[1], gx, nx);
-        const float v1 = diff3(r[-FW], r[0], r[FW], gy, ny);
-        q0 = to_q<WIDE>(quant(v0, g.qscale), st);
-        q1 = to_q<WIDE>(quant(v1, g.qscale), st);
-        facts &= fact_bits(q0, q1);
-      }
-      qs[par][0][e] = q0;
-      qs[par][1][e] = q1;
-    }
-  };
-
-  // Ordinal edge bits (masks x=1, y=2, xy=3) of plane parity par for the EH x EW anchors.
-  auto ordinal_edges = [&](int par) {
-    for (int e = tid; e < EH * EW; e += 256) {
-      int ly = e / EW, lx = e - ly * EW;
-      int qa = ly * QW + lx;
-      Q a0 = qs[par][0][qa], a1 = qs[par][1][qa];
-      unsigned w = 0;
-      w |= sos2_positive<Q>(a0, a1, qs[par][0][qa + 1], qs[par][1][qa + 1]) << 0;
-      w |= sos2_positive<Q>(a0, a1, qs[par][0][qa + QW], qs[par][1][qa + QW]) << 1;
-      w |= sos2_positive<Q>(a0, a1, qs[par][0][qa + QW + 1], qs[par][1][qa + QW + 1]) << 2;
-      ew[par][e] = (uint8_t)w;
-    }
-  };
-
-  // Interval edge bits (masks t=4, xt=5, yt=6, xyt=7) from plane parity par to par^1, OR-ed into ew[par].
-  auto interval_edges = [&](int par) {
-    const int nxp = par ^ 1;
-    for (int e = tid; e < EH * EW; e += 256) {
-      int ly = e / EW, lx = e - ly * EW;
-      int qa = ly * QW + lx;
-      Q a0 = qs[par][0][qa], a1 = qs[par][1][qa];
-      unsigned w = 0;
-      w |= sos2_positive<Q>(a0, a1, qs[nxp][0][qa], qs[nxp][1][qa]) << 3;
-      w |= sos2_positive<Q>(a0, a1, qs[nxp][0][qa + 1], qs[nxp][1][qa + 1]) << 4;
-      w |= sos2_positive<Q>(a0, a1, qs[nxp][0][qa + QW], qs[nxp][1][qa + QW]) << 5;
-      w |= sos2_positive<Q>(a0, a1, qs[nxp][0][qa + QW + 1], qs[nxp][1][qa + QW + 1]) << 6;
-      ew[par][e] |= (uint8_t)w;
-    }
-  };
-
-  // Narrow variant: one pass per position computes the ordinal edges of step t+1 (masks x, y, xy) and the interval
-  // edges t -> t+1 (masks t, xt, yt, xyt) from five vertex vectors converted to binary64 once.
-  auto fused_edges = [&](int par) {
-    const int nxp = par ^ 1;
-    for (int e = tid; e < EH * EW; e += 256) {
-      const int ly = e / EW, lx = e - ly * EW;
-      const int qa = ly * QW + lx;
-      const double a0 = (double)qs[par][0][qa], a1 = (double)qs[par][1][qa];
-      const double b0 = (double)qs[nxp][0][qa], b1 = (double)qs[nxp][1][qa];
-      const double c0 = (double)qs[nxp][0][qa + 1], c1 = (double)qs[nxp][1][qa + 1];
-      const double d0 = (double)qs[nxp][0][qa + QW], d1 = (double)qs[nxp][1][qa + QW];
-      const double f0 = (double)qs[nxp][0][qa + QW + 1], f1 = (double)qs[nxp][1][qa + QW + 1];
-      // edges (b c), (b d), (b f) -> ordinal bits 0-2 of step t+1; (a b), (a c), (a d), (a f) -> interval bits 3-6
-      const double P0[7] = {b0, b0, b0, a0, a0, a0, a0}, P1[7] = {b1, b1, b1, a1, a1, a1, a1};
-      const double Q0[7] = {c0, d0, f0, b0, c0, d0, f0}, Q1[7] = {c1, d1, f1, b1, c1, d1, f1};
-      unsigned bits = 0, zero = 0;
+      p.h[0] = rintf(w.h[0] * one);
+      p.h[1] = rintf(w.h[1] * one);
+    } else {
 #pragma unroll
-      for (int k = 0; k < 7; ++k) {
-        const double d = __builtin_fma(P0[k], Q1[k], -(P1[k] * Q0[k]));  // exact
-        bits |= (unsigned)(d > 0.0) << k;
-        zero |= (unsigned)(d == 0.0) << k;
+      for (int r = 0; r < kDetVec; ++r) {
+        const float f = w.r[r + 1];
+        nonfinite = __builtin_fmaf(f, 0.0f, nonfinite);
+        const float lo = from_prev(f, lane_value(w.h[0], r + 1)), hi = from_next(f, lane_value(w.h[2], r + 1));
+        const int y = y0 + r;
+        p.q[r][0] = rintf((hi - lo) * sx);
+        p.q[r][1] = rintf((w.r[r + 2] - w.r[r]) * __int_as_float((y == 0 || y >= ny - 1) ? one_bits : half_bits));
       }
-      if (zero) {  // the perturbation decides exact zeros only (rare on generic data)
-#pragma unroll
-        for (int k = 0; k < 7; ++k)
-          if ((zero >> k) & 1u) bits |= sos2_positive_d(P0[k], P1[k], Q0[k], Q1[k]) << k;
-      }
-      ew[nxp][e] = (uint8_t)(bits & 7u);
-      ew[par][e] |= (uint8_t)(bits & 0x78u);
+      p.h[0] = rintf((w.h[3] - w.h[1]) * sxh);
+      p.h[1] = rintf((row_next(w.h[2]) - row_prev(w.h[2])) * syh);
     }
-  };
-
-  // triangle lookup tables (LDS copy of the compile-time tables)
-  __shared__ unsigned short s_lut[8][128];
-  for (int i = tid; i < 8 * 128; i += 256) s_lut[i >> 7][i & 127] = kTri2Lut.t[i >> 7][i & 127];
-
-  // Sign facts of a plane's quantised vectors over the tile (anchors and their +1 neighbours, inside the grid):
-  // bit 0 every x component > 0, bit 1 every x < 0, bit 2 every y > 0, bit 3 every y < 0, bit 4 every vector zero.
-  // When a fact holds on both planes of a step, no triangle anchored in the tile at that step is punctured: a
-  // component of one strict sign at all three vertices keeps that sign under the symbolic perturbation (its
-  // entries move by infinitesimals only), so the origin is outside the triangle; and with all vectors zero every
-  // edge determinant takes the perturbation's last, negative term, so the three cofactor signs never agree.  The
-  // edge and triangle passes of such a step are skipped (its masks and counts are zero).
-  __shared__ unsigned s_fact[2];
-  __shared__ int s_ord_ok[2];  // the ordinal edge words of the plane slot have been computed
-  const int wave = tid >> 6, lane = tid & 63;
-  auto plane_facts = [&](int p) {  // block reduction of the facts gathered while the plane was quantised
-    const unsigned bits = facts;
-    facts = 0x1Fu;
-    unsigned wb = 0;
+    float mn[2] = {p.q[0][0], p.q[0][1]}, mx[2] = {p.q[0][0], p.q[0][1]};
 #pragma unroll
-    for (int k = 0; k < 5; ++k)
-      if (__ballot(!((bits >> k) & 1u)) == 0) wb |= 1u << k;
-    if (lane == 0) atomicAnd(&s_fact[p], wb);
+    for (int r = 1; r < kDetVec; ++r)  // rows past the grid repeat its last row, or are zero (no fact then)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        mn[c] = fminf(mn[c], p.q[r][c]);
+        mx[c] = fmaxf(mx[c], p.q[r][c]);
+      }
+    const float big = fmaxf(fmaxf(mx[0], -mn[0]), fmaxf(mx[1], -mn[1]));
+    if (big >= kNarrow2) st |= big >= 4611686018427387904.0f ? (ST_WIDE | ST_RANGE) : ST_WIDE;
+    const u64 off = ~below, hoff = ~h_in;  // lanes outside the grid
+    const u64 p0 = (__ballot(mn[0] > 0.0f) | off) & (__ballot(p.h[0] > 0.0f) | hoff);
+    const u64 n0 = (__ballot(mx[0] < 0.0f) | off) & (__ballot(p.h[0] < 0.0f) | hoff);
+    const u64 p1 = (__ballot(mn[1] > 0.0f) | off) & (__ballot(p.h[1] > 0.0f) | hoff);
+    const u64 n1 = (__ballot(mx[1] < 0.0f) | off) & (__ballot(p.h[1] < 0.0f) | hoff);
+    const u64 z = ((__ballot(fmaxf(mx[0], -mn[0]) == 0.0f) & __ballot(fmaxf(mx[1], -mn[1]) == 0.0f)) | off) &
+                  ((__ballot(p.h[0] == 0.0f) & __ballot(p.h[1] == 0.0f)) | hoff);
+    const unsigned f = (p0 == ~0ull ? 1u : 0u) | (n0 == ~0ull ? 2u : 0u) | (p1 == ~0ull ? 4u : 0u) |
+                       (n1 == ~0ull ? 8u : 0u) | (z == ~0ull ? 16u : 0u);
+    return f;
   };
 
-  // prologue: plane t0 (its ordinal edges are formed when a step first needs them)
-  if (tid == 0) {
-    s_fact[t0 & 1] = 0x1Fu;
-    s_ord_ok[0] = s_ord_ok[1] = 0;
-  }
-  __syncthreads();
-  load_plane(t0, t0 & 1);
-  __syncthreads();
-  quantise_plane(t0 & 1);
-  plane_facts(t0 & 1);
+  // ~0 where the edge (a, b) is negative, ties by the perturbation
+  auto edge = [&](double a0, double a1, double b0, double b1) -> int {
+    const double d = edge_det(a0, a1, b0, b1);
+    const int tie = edge_tie(a1, b0, b1), neg = edge_neg(d);
+    return d == 0.0 ? tie : neg;
+  };
+  // Edge signs of plane t carried from one step to the next, already spread: the own word of the ordinal edges x, y, xy
+  // of each row (row 8: x only) with a copy of the x and y signs in its free bits, and, lane-parallel, the y edges of
+  // the column x0+64.
+  constexpr int kBitX = 12, kBitY = 13;
+  constexpr unsigned kOwnX = kSpread.own[1] | 1u << kBitX, kOwnY = kSpread.own[2] | 1u << kBitY, kOwnXY = kSpread.own[3];
+  unsigned ord[kDetVec];
+  int ohy = 0;
+  auto ordinals = [&](const DetPlane& p) {
+    double a0 = p.q[0][0], a1 = p.q[0][1];
+    double c0 = from_next(p.q[0][0], lane_value(p.h[0], 1)), c1 = from_next(p.q[0][1], lane_value(p.h[1], 1));
+    int nx_ = edge(a0, a1, c0, c1);
+#pragma unroll
+    for (int r = 0; r < kDetRows; ++r) {
+      const double d0 = p.q[r + 1][0], d1 = p.q[r + 1][1];
+      c0 = from_next(p.q[r + 1][0], lane_value(p.h[0], r + 2));
+      c1 = from_next(p.q[r + 1][1], lane_value(p.h[1], r + 2));
+      ord[r] = spread(nx_, kOwnX, spread(edge(a0, a1, d0, d1), kOwnY, spread(edge(a0, a1, c0, c1), kOwnXY, 0u)));
+      nx_ = edge(d0, d1, c0, c1);
+      a0 = d0;
+      a1 = d1;
+    }
+    ord[kDetRows] = spread(nx_, kOwnX, 0u);
+    ohy = edge(p.h[0], p.h[1], row_next(p.h[0]), row_next(p.h[1]));
+  };
 
-  const int gx = x0 + lane;
+  DetRaw<VEC> raw;
+  DetPlane A, B;
+  load(t0, raw);
+  unsigned factA = quantise(raw, A);
+  if (t0 + 1 < nt) load(t0 + 1, raw);
+  bool have_ord = false;  // ord and ohy hold plane t's edges
+  const unsigned valid_x = gx < nx - 1 ? 0xFFFu : (gx < nx ? 0xFFFu & ~types_using(1) : 0u);
   for (int t = t0; t < t1; ++t) {
-    const int par = t & 1, nxp = par ^ 1;
-    const bool has_next = (t + 1 < nt);
-    __syncthreads();  // previous triangle pass done with ew / fs; facts and edge flags of plane t visible
+    const bool has_next = t + 1 < nt;
+    unsigned factB = 31u;
     if (has_next) {
-      if (tid == 0) s_fact[nxp] = 0x1Fu;  // ordered before the atomics by the barrier after the load
-      load_plane(t + 1, nxp);
-      __syncthreads();
-      quantise_plane(nxp);
-      plane_facts(nxp);
-      __syncthreads();  // quantised plane and its facts visible
+      factB = quantise(raw, B);
+      if (t + 1 < t1 && t + 2 < nt) load(t + 2, raw);
     }
-    const bool certified = (s_fact[par] & (has_next ? s_fact[nxp] : 0x1Fu)) != 0u;  // uniform
-    const bool ord_ok = s_ord_ok[par] != 0;
-    if (!certified) {
-      if (!ord_ok) ordinal_edges(par);  // each thread ORs into the words it assigned here
-      if (has_next) {
-        if constexpr (!WIDE) {
-          fused_edges(par);
-        } else {
-          ordinal_edges(nxp);
-          interval_edges(par);
+    const bool certified = (factA & factB) != 0u;  // uniform
+    const int y0 = first_row();
+    const long long seg0 = ((long long)mpl(g, t) * ny + y0) * g.nxt + bx;
+    char* mrow = (char*)(masks + ((long long)mpl(g, t) * ny + y0) * nx);
+    const unsigned mb = 2u * (unsigned)gx;
+    int cnt = 0;  // lane r: hits of row r
+    if (certified) {
+#pragma unroll
+      for (int r = 0; r < kDetRows; ++r) {
+        if (y0 + r < ny && gx < nx) *(uint16_t*)(mrow + mb) = 0;
+        mrow += row_bytes / 2;
+      }
+      have_ord = false;
+    } else {
+      if (!have_ord) ordinals(A);
+      if (!has_next) B = A;  // no step t + 1: only the ordinal triangles are valid
+      // the column x0+64, lane r + 1 = row r: the word its edges y, t, yt (and y of plane t + 1) pass to lane 63
+      unsigned hg;
+      {
+        const double ha0 = A.h[0], ha1 = A.h[1], hb0 = B.h[0], hb1 = B.h[1];
+        const double hn0 = row_next(B.h[0]), hn1 = row_next(B.h[1]);
+        const int hby = edge(hb0, hb1, hn0, hn1);
+        hg = spread(ohy, kSpread.g[2], 0u);
+        hg = spread(edge(ha0, ha1, hb0, hb1), kSpread.g[4] | kGXy, hg);
+        hg = spread(edge(ha0, ha1, hn0, hn1), kSpread.g[6], hg);
+        hg = spread(hby, kSpread.gt[2], hg);
+        ohy = hby;
+      }
+      // rolling over the rows: b, c = plane t+1 at (x, r), (x+1, r); d, f = at row r + 1; a, e = plane t at (x, r), r + 1
+      double b0 = B.q[0][0], b1 = B.q[0][1];
+      double c0 = from_next(B.q[0][0], lane_value(B.h[0], 1)), c1 = from_next(B.q[0][1], lane_value(B.h[1], 1));
+      double a0 = A.q[0][0], a1 = A.q[0][1];
+      int T = edge(a0, a1, b0, b1), XT = edge(a0, a1, c0, c1), bX = edge(b0, b1, c0, c1);
+      unsigned e0_prev = 0, own_prev = 0;  // the row below, whose E0 still lacks the bits of this row
+#pragma unroll
+      for (int r = 0; r <= kDetRows; ++r) {
+        // row r of the window: edges t, xt of plane t, x of plane t+1 (T, XT, bX); rows 0..7 also y, xy, yt, xyt
+        int YT = 0, XYT = 0, bY = 0, bXY = 0, Tn = 0, XTn = 0, bXn = 0;
+        if (r < kDetRows) {
+          const double d0 = B.q[r + 1][0], d1 = B.q[r + 1][1];
+          const double f0 = from_next(B.q[r + 1][0], lane_value(B.h[0], r + 2));
+          const double f1 = from_next(B.q[r + 1][1], lane_value(B.h[1], r + 2));
+          const double e0 = A.q[r + 1][0], e1 = A.q[r + 1][1];
+          const double dYT = edge_det(a0, a1, d0, d1), dXYT = edge_det(a0, a1, f0, f1);
+          const double dbY = edge_det(b0, b1, d0, d1), dbXY = edge_det(b0, b1, f0, f1);
+          const double dbX = edge_det(d0, d1, f0, f1);
+          const double dT = edge_det(e0, e1, d0, d1), dXT = edge_det(e0, e1, f0, f1);
+          YT = edge_neg(dYT);
+          XYT = edge_neg(dXYT);
+          bY = edge_neg(dbY);
+          bXY = edge_neg(dbXY);
+          bXn = edge_neg(dbX);
+          Tn = edge_neg(dT);
+          XTn = edge_neg(dXT);
+          float z = zero_seen(1.0f, dYT, dXYT);
+          z = zero_seen(z, dbY, dbXY);
+          z = zero_seen(z, dbX, dT);
+          z = zero_seen(z, dXT, dXT);
+          auto settle = [](int& neg, double d, int tie) { neg = d == 0.0 ? tie : neg; };
+          if (__ballot(z == 0.0f)) {  // exact zeros are rare on generic data
+            settle(YT, dYT, edge_tie(a1, d0, d1));
+            settle(XYT, dXYT, edge_tie(a1, f0, f1));
+            settle(bY, dbY, edge_tie(b1, d0, d1));
+            settle(bXY, dbXY, edge_tie(b1, f0, f1));
+            settle(bXn, dbX, edge_tie(d1, f0, f1));
+            settle(Tn, dT, edge_tie(e1, d0, d1));
+            settle(XTn, dXT, edge_tie(e1, f0, f1));
+          }
+          a0 = e0;
+          a1 = e1;
+          b0 = d0;
+          b1 = d1;
         }
+        const unsigned o = ord[r];
+        // what the row's edges give to the anchors at x - 1 (and x - 1, y - 1)
+        unsigned gw = ((o >> kBitY) & 1u) * kSpread.g[2];
+        gw = spread(T, kSpread.g[4] | kGXy, gw);
+        gw = spread(YT, kSpread.g[6], gw);
+        gw = spread(bY, kSpread.gt[2], gw);
+        gw = from_next(gw, (unsigned)__builtin_amdgcn_readlane((int)hg, r + 1));
+        if (r > 0) {
+          // the row below is complete with this row's x, t, xt (and x of plane t+1) edges
+          unsigned hw = ((o >> kBitX) & 1u) * kSpread.h[1];
+          hw = spread(T, kSpread.h[4], hw);
+          hw = spread(XT, kSpread.h[5], hw);
+          hw = spread(bX, kSpread.ht[1], hw);
+          const unsigned E0 = e0_prev | (gw & kGXy) | hw;
+          // uniform: types that need the next row or step (rows past the grid: none)
+          const int y = y0 + r - 1;
+          const unsigned vt = has_next ? 0xFFFu : 0xFFFu & ~types_using(4);
+          const unsigned vy = y < ny - 1 ? 0xFFFu : (y < ny ? 0xFFFu & ~types_using(2) : 0u);
+          const unsigned m = ~(E0 ^ own_prev) & ((own_prev >> 16) ^ E0) & valid_x & (vt & vy);
+          if (__ballot(m != 0u)) {
+            const unsigned n = wave_sum((unsigned)__popc(m));
+            cnt |= __builtin_amdgcn_inverse_ballot_w64(1ull << (r - 1)) ? (int)n : 0;
+          }
+          if (y < ny && gx < nx) *(uint16_t*)(mrow + mb) = (uint16_t)m;
+          mrow += row_bytes / 2;
+        }
+        if (r < kDetRows) {
+          unsigned own = spread(T, kSpread.own[4], o);
+          own = spread(XT, kSpread.own[5], own);
+          own = spread(YT, kSpread.own[6], own);
+          own_prev = spread(XYT, kSpread.own[7], own);
+          unsigned kw = spread(bX, kSpread.k[1], gw & kGOwn);
+          kw = spread(bY, kSpread.k[2], kw);
+          e0_prev = spread(bXY, kSpread.k[3], kw);
+          ord[r] = spread(bX, kOwnX, spread(bY, kOwnY, spread(bXY, kOwnXY, 0u)));
+        } else {
+          ord[r] = spread(bX, kOwnX, 0u);
+        }
+        T = Tn;
+        XT = XTn;
+        bX = bXn;
+        __builtin_amdgcn_sched_barrier(0);  // rows are not interleaved: their registers would not fit
       }
+      have_ord = true;
     }
-    __syncthreads();
-    if (tid == 0 && has_next) s_ord_ok[nxp] = certified ? 0 : 1;
-
-    // triangle tests: wave w handles rows w, w+4, ...
-    for (int ly = wave; ly < TY; ly += 4) {
-      const int gy = y0 + ly;
-      unsigned m = 0;
-      if (gx < nx && gy < ny && !certified) {
-        const int a = ly * EW + lane;
-        // word of the anchor and of its neighbours p + e(M1): plane t for M1 in {x, y, xy}, plane t+1 (ordinal
-        // bits only) for M1 in {t, xt, yt}
-        // sides opposite v0, v1, v2 of triangle (M1, M2): edges (v1 v2) = (p + e(M1), M2), (v0 v2) = (p, M1|M2),
-        // (v0 v1) = (p, M1); cofactor signs +S(v1v2), -S(v0v2), +S(v0v1): punctured iff S(v1v2) = S(v0v1) != S(v0v2).
-        // The 12 tests run bit-parallel: E0/E1/E2 gather, for every type, the sign bit of its edge opposite
-        // v0/v1/v2 through 128-entry tables indexed by the 7-bit edge words.
-        const unsigned W0 = ew[par][a];
-        unsigned E0 = s_lut[2][ew[par][a + 1]] | s_lut[3][ew[par][a + EW]] | s_lut[4][ew[par][a + EW + 1]];
-        if (has_next) E0 |= s_lut[5][ew[nxp][a]] | s_lut[6][ew[nxp][a + 1]] | s_lut[7][ew[nxp][a + EW]];
-        const unsigned E1 = s_lut[1][W0], E2 = s_lut[0][W0];
-        m = ~(E0 ^ E2) & (E1 ^ E0) & 0xFFFu;
-        unsigned valid = 0xFFFu;
-        if (gx == nx - 1) valid &= ~kUseX;
-        if (gy == ny - 1) valid &= ~kUseY;
-        if (t == nt - 1) valid &= ~kUseT;
-        m &= valid;
-      }
-      if (gx < nx && gy < ny) masks[((long long)mpl(g, t) * ny + gy) * nx + gx] = (uint16_t)m;
-      unsigned c = wave_sum(__popc(m));
-      if (lane == 0 && gy < ny) seg_cnt[((long long)mpl(g, t) * ny + gy) * g.nxt + bx] = (int)c;
-    }
+    if (lane < kDetRows && y0 + lane < ny) seg_cnt[seg0 + (long long)lane * g.nxt] = cnt;
+    A = B;
+    factA = factB;
   }
+  if (!(nonfinite == 0.0f)) st |= ST_NONFINITE;
   if (st) atomicOr(status, st);
 }
 
-template <int TY, bool WIDE>
-__global__ __launch_bounds__(256) void detect2d(Grid2 g, int TT, uint16_t* __restrict__ masks,
+// grid = (ceil(nx / 64), ceil(ny / rows per block), ceil(nt / TT)), block = 64 lanes x (rows per block / rows per wavefront) wavefronts
+template <bool VEC>
+__global__ __launch_bounds__(64 * 32 / kDetRows) __attribute__((amdgpu_waves_per_eu(3))) void detect2d(Grid2 g, int TT, uint16_t* __restrict__ masks,
                                                 int* __restrict__ seg_cnt, unsigned* __restrict__ status) {
-  detect2d_tile<TY, WIDE>(g, TT, blockIdx.x, blockIdx.y, blockIdx.z, masks, seg_cnt, status);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int y0 = ((int)blockIdx.y * (int)(blockDim.x >> 6) + w) * kDetRows;
+  if (y0 < g.ny) detect2d_wave<VEC>(g, TT, blockIdx.x, y0, blockIdx.z, masks, seg_cnt, status);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1586,20 +1690,22 @@ __device__ __forceinline__ int series_of(const int* prefix, int nser, int item) 
   return lo;
 }
 
-template <int TY, bool WIDE>
-__global__ __launch_bounds__(256) void detect2d_batched(const Series2* __restrict__ S, const int* __restrict__ prefix,
+// Detection: every wavefront pulls its own items (its tiles are independent of its workgroup's).
+template <bool VEC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void detect2d_batched(const Series2* __restrict__ S, const int* __restrict__ prefix,
                                                         int nser, int TT, int* counter, unsigned* status) {
-  __shared__ int s_item;
   const int total = prefix[nser];
   for (;;) {
-    const int it = take_item(counter, total, &s_item);
-    if (it < 0) break;
+    int it = 0;
+    if (lane_id() == 0) it = atomicAdd(counter, 1);
+    it = __builtin_amdgcn_readfirstlane(it);
+    if (it >= total) break;
     const int s = series_of(prefix, nser, it);
     const Grid2 g = S[s].g;
     const int local = it - prefix[s];
-    const int tx = g.nxt, tyn = (g.ny + TY - 1) / TY;
+    const int tx = g.nxt, tyn = (g.ny + kDetRows - 1) / kDetRows;
     const int bx = local % tx, by = (local / tx) % tyn, bz = local / (tx * tyn);
-    detect2d_tile<TY, WIDE>(g, TT, bx, by, bz, S[s].masks, S[s].seg_cnt, status);
+    detect2d_wave<VEC>(g, TT, bx, by * kDetRows, bz, S[s].masks, S[s].seg_cnt, status);
   }
 }
 
@@ -1674,14 +1780,15 @@ hipError_t launch_emit2d_steps(const Grid2& g, bool wide, const uint16_t* masks,
   return hipGetLastError();
 }
 
-hipError_t launch_detect2d_batched(const Series2* S, const int* prefix, int nser, int total_items, int tt, bool wide,
+hipError_t launch_detect2d_batched(const Series2* S, const int* prefix, int nser, int total_items, int tt, int kind,
                                    int* counter, unsigned* status, hipStream_t s) {
-  int blocks = total_items < 2048 ? total_items : 2048;
+  int blocks = (total_items + 3) / 4;
+  if (blocks > 1024) blocks = 1024;  // four wavefronts per SIMD
   if (blocks < 1) blocks = 1;
-  if (wide)
-    detect2d_batched<16, true><<<blocks, 256, 0, s>>>(S, prefix, nser, tt, counter, status);
+  if (kind != 0)
+    detect2d_batched<true><<<blocks, 256, 0, s>>>(S, prefix, nser, tt, counter, status);
   else
-    detect2d_batched<16, false><<<blocks, 256, 0, s>>>(S, prefix, nser, tt, counter, status);
+    detect2d_batched<false><<<blocks, 256, 0, s>>>(S, prefix, nser, tt, counter, status);
   return hipGetLastError();
 }
 
@@ -1699,25 +1806,14 @@ hipError_t launch_emit2d_batched(const Series2* S, const int* prefix, int nser, 
 // ---------------------------------------------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------------------------------------------
-hipError_t launch_detect2d(const Grid2& g, int ty, int tt, bool wide, uint16_t* masks, int* seg_cnt,
-                           unsigned* status, hipStream_t s) {
+hipError_t launch_detect2d(const Grid2& g, int ty, int tt, uint16_t* masks, int* seg_cnt, unsigned* status,
+                           hipStream_t s) {
   dim3 grid((unsigned)g.nxt, (unsigned)((g.ny + ty - 1) / ty), (unsigned)((g.t_end - g.t_begin + tt - 1) / tt));
-  if (ty == 8) {
-    if (wide)
-      detect2d<8, true><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, status);
-    else
-      detect2d<8, false><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, status);
-  } else if (ty == 16) {
-    if (wide)
-      detect2d<16, true><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, status);
-    else
-      detect2d<16, false><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, status);
-  } else {
-    if (wide)
-      detect2d<32, true><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, status);
-    else
-      detect2d<32, false><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, status);
-  }
+  const unsigned threads = 64u * (unsigned)(ty / kDetRows);
+  if (g.kind != 0)
+    detect2d<true><<<grid, threads, 0, s>>>(g, tt, masks, seg_cnt, status);
+  else
+    detect2d<false><<<grid, threads, 0, s>>>(g, tt, masks, seg_cnt, status);
   return hipGetLastError();
 }
 

@@ -74,8 +74,11 @@ struct Out3 {
   uint2* work;
 };
 
-hipError_t launch_detect2d(const Grid2& g, int ty, int tt, bool wide, uint16_t* masks, int* seg_cnt,
-                           unsigned* status, hipStream_t s);
+constexpr int kDetectRows = 8;  // anchor rows of a detection wavefront
+// Detection; ty: anchor rows per workgroup (8, 16 or 32), tt: steps per slab.  Sets ST_WIDE when a component reaches
+// 2^24 (the emission then takes its 128-bit form) and ST_RANGE when one reaches 2^62.
+hipError_t launch_detect2d(const Grid2& g, int ty, int tt, uint16_t* masks, int* seg_cnt, unsigned* status,
+                           hipStream_t s);
 hipError_t launch_emit2d(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
                          const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
                          hipStream_t s);
@@ -92,7 +95,7 @@ hipError_t launch_emit2d_sparse_batched(const Series2* S, const long long* bpref
 hipError_t launch_emit2d_steps(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
                                const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
                                hipStream_t s);
-hipError_t launch_detect2d_batched(const Series2* S, const int* prefix, int nser, int total_items, int tt, bool wide,
+hipError_t launch_detect2d_batched(const Series2* S, const int* prefix, int nser, int total_items, int tt, int kind,
                                    int* counter, unsigned* status, hipStream_t s);
 hipError_t launch_emit2d_batched(const Series2* S, const int* prefix, int nser, int total_items, bool wide,
                                  int* counter, unsigned* status, unsigned long long* work_cnt, hipStream_t s);
