@@ -1922,31 +1922,28 @@ ftk_status ftk_track_iso3d(const float* field, int64_t nx, int64_t ny, int64_t n
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
   const long long V = nx * ny * nz * nt;
-  const long long G = (V + 15) / 16;  // groups of 16 vertices (offsets: one base per group)
-  unsigned short* emask = sc.get<unsigned short>((size_t)V);
-  unsigned char* hcnt = sc.get<unsigned char>((size_t)G * 16);
-  unsigned char* tcnt = sc.get<unsigned char>((size_t)G * 16);
-  int* gsum = sc.get<int>((size_t)G);
-  long long* hbase = sc.get<long long>((size_t)G);
-  long long* tbase = sc.get<long long>((size_t)G);
-  long long* abase = sc.get<long long>((size_t)G);
-  unsigned long long* bits = sc.get<unsigned long long>((size_t)((nx + 63) / 64) * ny * nz * nt);
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(G));
+  const long long NW = ((nx + 63) / 64) * ny * nz * nt;  // words of 64 vertices of a row
+  unsigned long long* bits = sc.get<unsigned long long>((size_t)NW);
+  int* cnt = sc.get<int>((size_t)NW * 3);  // crossings, cubes with tetrahedra, runs of equal sides
+  long long* base = sc.get<long long>((size_t)NW * 3);
+  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(NW));
   Ctl* dctl = sc.get<Ctl>(1);
-  if (!emask || !hcnt || !tcnt || !gsum || !hbase || !tbase || !abase || !bits || !tmp || !dctl)
-    return fail(FTK_ERR_OOM, "scratch allocation failed");
+  if (!bits || !cnt || !base || !tmp || !dctl) return fail(FTK_ERR_OOM, "scratch allocation failed");
+  int *hcnt = cnt, *acnt = cnt + NW, *rcnt = cnt + 2 * NW;
+  long long *hbase = base, *abase = base + NW, *rbase = base + 2 * NW;
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
-  HIP_TRY(ftk::launch_iso_count(field, (int)nx, (int)ny, (int)nz, (int)nt, isovalue, bits, emask, hcnt, tcnt,
-                                &dctl->status, s));
-  HIP_TRY(ftk::launch_group16_bases(hcnt, V, false, gsum, hbase, &dctl->total, tmp, s));
-  HIP_TRY(ftk::launch_group16_bases(tcnt, V, false, gsum, tbase, (long long*)&dctl->cnt[ftk::CNT_LIST], tmp, s));
-  HIP_TRY(ftk::launch_group16_bases(tcnt, V, true, gsum, abase, (long long*)&dctl->cnt[ftk::CNT_WORK], tmp, s));
+  HIP_TRY(ftk::launch_iso_count(field, (int)nx, (int)ny, (int)nz, (int)nt, isovalue, bits, hcnt, acnt, rcnt,
+                                &dctl->cnt[ftk::CNT_LIST], &dctl->status, s));
+  HIP_TRY(ftk::launch_scan(hcnt, hbase, NW, &dctl->total, tmp, s));
+  HIP_TRY(ftk::launch_scan(acnt, abase, NW, (long long*)&dctl->cnt[ftk::CNT_WORK], tmp, s));
+  HIP_TRY(ftk::launch_scan(rcnt, rbase, NW, (long long*)&dctl->cnt[ftk::CNT_LINKED], tmp, s));
   Ctl h;
   ftk_status st = read_ctl(&h, dctl, s);
   if (st) return st;
   st = decode_status(h.status);
   if (st) return st;
   const long long nh = h.total, ntets = (long long)h.cnt[ftk::CNT_LIST], nact = (long long)h.cnt[ftk::CNT_WORK];
+  const long long nruns = (long long)h.cnt[ftk::CNT_LINKED];
   if (nh > 0x7fffffffll) return fail(FTK_ERR_CAPACITY, "%lld crossed edges exceed the 32-bit tetrahedron indices", nh);
   ftk_iso_result r;
   std::memset(&r, 0, sizeof(r));
@@ -1956,9 +1953,18 @@ ftk_status ftk_track_iso3d(const float* field, int64_t nx, int64_t ny, int64_t n
   r.pos = (float*)al.get(sizeof(float) * 4 * (size_t)(nh > 0 ? nh : 1));
   r.label = (int64_t*)al.get(sizeof(int64_t) * (size_t)(nh > 0 ? nh : 1));
   r.tets = (int32_t*)al.get(sizeof(int32_t) * 4 * (size_t)(ntets > 0 ? ntets : 1));
-  unsigned* parent = sc.get<unsigned>((size_t)(nh > 0 ? nh : 1));
-  long long* active = sc.get<long long>((size_t)(nact > 0 ? nact : 1));
-  if (!r.edge_id || !r.pos || !r.label || !r.tets || !parent || !active) {
+  // nothing below is needed, and runs are not numbered beyond 32 bits, without crossings
+  const bool any = nh > 0;
+  unsigned* vinfo = sc.get<unsigned>((size_t)(any ? V : 1));
+  unsigned* hcomp = sc.get<unsigned>((size_t)(any ? nh : 1));
+  long long* list = sc.get<long long>((size_t)(any ? nact : 1));
+  const long long ngrp = (nact + 63) / 64;
+  int* tcnt = sc.get<int>((size_t)(any ? ngrp : 1));
+  long long* tbase = sc.get<long long>((size_t)(any ? ngrp + 1 : 1));
+  unsigned* runs = sc.get<unsigned>((size_t)(any ? 2 * nruns : 1));
+  long long* first = sc.get<long long>((size_t)(any ? nruns : 1));
+  if (!r.edge_id || !r.pos || !r.label || !r.tets || !vinfo || !hcomp || !list || !tcnt || !tbase || !runs ||
+      !first) {
     ftk_iso_result_free(&r, opt, stream);
     return fail(FTK_ERR_OOM, "output allocation failed");
   }
@@ -1968,14 +1974,12 @@ ftk_status ftk_track_iso3d(const float* field, int64_t nx, int64_t ny, int64_t n
   }
   hipError_t he = hipSuccess;
   if (nh > 0) {
-    he = ftk::launch_iso_emit(field, (int)nx, (int)ny, (int)nz, (int)nt, isovalue, emask, hbase, hcnt,
-                              (long long*)r.edge_id, r.pos, parent, s);
-    if (he == hipSuccess) he = ftk::launch_iso_active(tcnt, abase, V, active, s);
+    he = ftk::launch_iso_components((int)nx, (int)ny, (int)nz, (int)nt, bits, rbase, nruns, runs, runs + nruns, first,
+                                    &dctl->cnt[ftk::CNT_TRAJ], s);
     if (he == hipSuccess)
-      he = ftk::launch_iso_unite(field, (int)nx, (int)ny, (int)nz, (int)nt, isovalue, bits, active, nact, emask, hbase,
-                                 hcnt, tcnt, tbase, parent, (int*)r.tets, &dctl->status, s);
-    if (he == hipSuccess)
-      he = ftk::launch_uf_label(parent, (const long long*)r.edge_id, (long long*)r.label, nh, dctl->cnt, s);
+      he = ftk::launch_iso_emit(field, (int)nx, (int)ny, (int)nz, (int)nt, isovalue, bits, hcnt, hbase, abase, rbase,
+                                runs + nruns, nh, nact, vinfo, (long long*)r.edge_id, r.pos, hcomp, first, list, tcnt,
+                                tbase, tmp, (int*)r.tets, (long long*)r.label, s);
   }
   if (he != hipSuccess) {
     ftk_iso_result_free(&r, opt, stream);
@@ -1987,7 +1991,7 @@ ftk_status ftk_track_iso3d(const float* field, int64_t nx, int64_t ny, int64_t n
     ftk_iso_result_free(&r, opt, stream);
     return st;
   }
-  r.n_components = (long long)h.cnt[ftk::CNT_TRAJ];
+  r.n_components = nh > 0 ? (long long)h.cnt[ftk::CNT_TRAJ] - 1 : 0;  // one below each vertex component but the first
   *out = r;
   return FTK_OK;
 }

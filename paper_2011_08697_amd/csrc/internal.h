@@ -158,27 +158,28 @@ hipError_t launch_order_place(int n, const int64_t* dims_with_t, const long long
                               const long long* roots, const long long* rb, const long long* offsets,
                               const unsigned char* is_ruler, const int* rid, const unsigned* seg, const int* st,
                               long long* order, unsigned* status, hipStream_t s);
-// Isovolume tracking (iso.hip): per-vertex crossing masks and hit / tetrahedron counts; emission of edge ids,
-// positions and identity parents from the scanned counts; pentachoron unions and tetrahedra over the active
-// vertices.  Per-vertex grids launch as (ceil(nx / 128), ny, nz * nt) blocks (ny, nz * nt <= 65535).
-// bits: ceil(nx / 64) * ny * nz * nt words of vertex sides, written by the count launch, read by the unite launch
+// Isovolume tracking (iso.hip).  Words of 64 vertices of a row (ceil(nx / 64) * ny * nz * nt of them) carry the sides
+// (bits) and the counts of crossings, cubes with tetrahedra and runs of equal sides, whose exclusive scans are hbase,
+// abase, rbase; *n_tets += the tetrahedra.
 hipError_t launch_iso_count(const float* f, int nx, int ny, int nz, int nt, float c, unsigned long long* bits,
-                            unsigned short* emask, unsigned char* hcnt, unsigned char* tcnt, unsigned* status,
+                            int* hcnt, int* acnt, int* rcnt, unsigned long long* n_tets, unsigned* status,
                             hipStream_t s);
-hipError_t launch_iso_emit(const float* f, int nx, int ny, int nz, int nt, float c, const unsigned short* emask,
-                           const long long* hbase, const unsigned char* hcnt, long long* edge_id, float* pos,
-                           unsigned* parent, hipStream_t s);
-// ascending list of the vertices with tetrahedra (tcnt > 0), at their offsets from abase (nonzero counts)
-hipError_t launch_iso_active(const unsigned char* tcnt, const long long* abase, long long V, long long* list,
-                             hipStream_t s);
-hipError_t launch_iso_unite(const float* f, int nx, int ny, int nz, int nt, float c,
-                            const unsigned long long* bits, const long long* active, long long n_active,
-                            const unsigned short* emask, const long long* hbase, const unsigned char* hcnt,
-                            const unsigned char* tcnt, const long long* tbase, unsigned* parent, int* tets,
-                            unsigned* status, hipStream_t s);
+// Component of every run (comp, n_runs; parent: scratch of n_runs), *n_comp += their number, first (n_runs) cleared.
+hipError_t launch_iso_components(int nx, int ny, int nz, int nt, const unsigned long long* bits,
+                                 const long long* rbase, long long n_runs, unsigned* parent, unsigned* comp,
+                                 long long* first, unsigned long long* n_comp, hipStream_t s);
+// Crossings with their points and labels, tetrahedra.  Scratch: vinfo (one word per vertex: hits before it in its word
+// | crossing mask << 16), hcomp (n_hits), list (n_active cubes), and per 64 of them tcnt and tbase (one entry more), with
+// scan_tmp for that many.
+hipError_t launch_iso_emit(const float* f, int nx, int ny, int nz, int nt, float c, const unsigned long long* bits,
+                           const int* hcnt, const long long* hbase, const long long* abase, const long long* rbase,
+                           const unsigned* comp, long long n_hits, long long n_active, unsigned* vinfo,
+                           long long* edge_id, float* pos, unsigned* hcomp, long long* first, long long* list,
+                           int* tcnt, long long* tbase, long long* scan_tmp, int* tets, long long* label,
+                           hipStream_t s);
 
 // Quantum vortex surfaces (vortex.hip): edge signs and positive-triangle masks (tmask, 50 bits) with per-vertex
-// counts; then emission of triangle ids, points and identity parents, and the pentachoron unions.  Grids as iso.
+// counts; then emission of triangle ids, points and identity parents, and the pentachoron unions.  Grids of (ceil(nx / 128), ny, nz * nt) blocks (ny, nz * nt <= 65535).
 hipError_t launch_vx_detect(const float* psi, int nx, int ny, int nz, int nt, float qscale, unsigned short* emask,
                             unsigned long long* tmask, unsigned char* cnt, unsigned* status, hipStream_t s);
 hipError_t launch_vx_emit(const float* psi, int nx, int ny, int nz, int nt, float qscale,

@@ -7,21 +7,32 @@
 //
 //   iso_bits  -- the side of the level set of every vertex as one bit, 64 per word (a value equal to the isovalue
 //                lies above it: the symbolic perturbation of a single entry is positive, Sec. 6.2).
-//   iso_count -- one lane per vertex: the sides at the 16 corners of its unit 4-cube (from the bit words),
-//                the crossing mask of its 15 edges, and the tetrahedra of its 24 pentachora (case I: one vertex on
-//                its side, 1 tetrahedron; case II: two, 3 tetrahedra).
-//   iso_emit  -- edge ids and intersection points p + mu e(M), mu = (c - f(p)) / (f(q) - f(p)), from the scanned
-//                counts; union-find parents start as the identity.
-//   iso_unite -- per 4-cube with crossings (compacted list): unite its crossed edges group by group (CAS hooking,
-//                larger root under the smaller), and per pentachoron write its tetrahedra (indices of crossed
-//                edges): case I the four edges of the lone vertex in chain order; case II the prism pair x triple
-//                split along the three monotone paths (staircase), which matches on the quadrilateral shared with
-//                the neighbouring pentachoron.
-// Labels (smallest edge id of each isovolume) come from the shared union-find label kernel.
+//   iso_count -- one lane per word: crossings, tetrahedra (case I: one vertex on its side, 1 tetrahedron; case II: two,
+//                3 tetrahedra), cubes with tetrahedra and runs of its 64 vertices, bit-parallel on the words of the 16
+//                corners of their unit 4-cubes.
+//   iso_runs_* - connected components of the vertices on one side of the level set, over runs of equal sides along x.
+//   iso_emit  -- edge ids, intersection points p + mu e(M), mu = (c - f(p)) / (f(q) - f(p)), and the component of
+//                every crossing, for the words that have any; the list of the cubes with tetrahedra.
+//   iso_tess  -- per listed cube, its tetrahedra (indices of crossed edges): case I the four edges of the lone vertex
+//                in chain order; case II the prism pair x triple split along the three monotone paths (staircase),
+//                which matches on the quadrilateral shared with the neighbouring pentachoron.
+//   iso_label -- the smallest edge id of each crossing's component.
+//
+// Isovolumes from vertex components.  An isovolume is a set of crossed edges connected through triangles (a triangle
+// has no or two crossed edges; the crossed edges of one simplex are connected through its triangles).  The mesh of a
+// box has no first cohomology, so the indicator of an isovolume -- two or no edges of every triangle -- is the
+// coboundary of a vertex function that changes exactly across its edges.  Hence (1) the crossed edges between two
+// vertex components belong to one isovolume (the function is constant on a component, so it differs on both or on
+// none), (2) an isovolume joins one pair of components only (crossed edges of a triangle share a vertex, and their
+// other ends are neighbours on one side), and (3) components and isovolumes form a tree.  Let v be the first vertex (in
+// the global order) of a component other than that of vertex 0: its lower neighbours v - e(M) are all across the level
+// and are neighbours of the lowest of them, so they lie in one component, whose first vertex is smaller.  The tree is
+// rooted that way, and every isovolume is the one below exactly one component: of the two components that a crossed
+// edge joins, the one whose first vertex is larger.  So an isovolume is named by that component, and there is one less
+// of them than components.  The union-find runs on a few million runs instead of the crossed edges.
 #include <utility>
 
 #include "common.h"
-#include "offsets16.h"
 #include "internal.h"
 #include "kuhn.h"
 #include "uf_cached.h"
@@ -30,7 +41,6 @@ namespace ftk {
 
 namespace {
 
-constexpr int kIsoBX = 128;  // lanes per block along x
 
 // chain corners of the 24 pentachoron types: corner k = s1 | ... | sk
 struct PenCorners {
@@ -49,59 +59,6 @@ constexpr PenCorners build_pen_corners() {
   return r;
 }
 
-// The edges of a 4-cube's pentachora are its 65 corner pairs a < a | M (a & M == 0, M != 0).  idx[a][M] is the local
-// index (255 for no edge), ea / eM its anchor corner and mask, side[pt] the 65-bit set (two words) of the 10 edges of
-// pentachoron type pt.
-constexpr int kCubeEdgeN = 65;
-struct CubeEdges {
-  unsigned char idx[16][16];
-  unsigned char ea[kCubeEdgeN], eM[kCubeEdgeN];
-  unsigned long long side[24][2];
-};
-constexpr CubeEdges build_cube_edges() {
-  CubeEdges r{};
-  int k = 0;
-  for (int a = 0; a < 16; ++a)
-    for (int M = 0; M < 16; ++M) r.idx[a][M] = 255;
-  for (int a = 0; a < 16; ++a)
-    for (int M = 1; M < 16; ++M)
-      if (!(a & M) && k < kCubeEdgeN) {
-        r.idx[a][M] = (unsigned char)k;
-        r.ea[k] = (unsigned char)a;
-        r.eM[k] = (unsigned char)M;
-        ++k;
-      }
-  for (int pt = 0; pt < 24; ++pt) {
-    int c[5] = {0, 0, 0, 0, 0};
-    for (int i = 0; i < 4; ++i) c[i + 1] = c[i] | kPen3.m[pt][i];
-    for (int i = 0; i < 5; ++i)
-      for (int j = i + 1; j < 5; ++j) {
-        const int l = r.idx[c[i]][c[j] ^ c[i]];
-        r.side[pt][l >> 6] |= 1ull << (l & 63);
-      }
-  }
-  return r;
-}
-constexpr int count_cube_edges() {
-  int k = 0;
-  for (int a = 0; a < 16; ++a)
-    for (int M = 1; M < 16; ++M) k += !(a & M);
-  return k;
-}
-static_assert(count_cube_edges() == kCubeEdgeN, "65 corner pairs (edges) per 4-cube");
-__constant__ CubeEdges kCubeEdges = build_cube_edges();
-
-typedef unsigned __int128 u128;
-
-__device__ __forceinline__ u128 edge_side_set(int pt) {
-  return ((u128)kCubeEdges.side[pt][1] << 64) | (u128)kCubeEdges.side[pt][0];
-}
-
-__device__ __forceinline__ int low_bit128(u128 m) {
-  const unsigned long long lo = (unsigned long long)m;
-  return lo ? __ffsll((long long)lo) - 1 : 64 + __ffsll((long long)(unsigned long long)(m >> 64)) - 1;
-}
-
 struct IsoGrid {
   const float* f;
   int nx, ny, nz, nt;
@@ -109,10 +66,6 @@ struct IsoGrid {
   const unsigned long long* bits;  // side of every vertex, one bit per vertex: row-major 64-vertex words
   int nwx;                         // words per row, ceil(nx / 64)
 };
-
-__device__ __forceinline__ long long vidx(const IsoGrid& g, int x, int y, int z, int t) {
-  return (((long long)t * g.nz + z) * g.ny + y) * g.nx + x;
-}
 
 // Side of every vertex as one bit (a value equal to the isovalue counts as above), packed per 64 vertices of a row
 // by a wave ballot: the passes that need the 16 corners of a 4-cube read these words (L2-resident, shared by
@@ -144,25 +97,62 @@ __global__ __launch_bounds__(256) void iso_bits(IsoGrid g, long long n_words, un
   if (bad) atomicOr(status, bad);
 }
 
-// above bits of the 16 cube corners (bit cm) and their validity (bit cm: corner in the grid)
-__device__ __forceinline__ void corner_bits(const IsoGrid& g, int x, int y, int z, int t, unsigned& above,
-                                            unsigned& valid) {
-  above = 0;
-  valid = 0;
-  unsigned long long w[16];
+typedef unsigned long long u64;
+
+// Row of a word and which of its upper neighbours (y, z, t) are in the grid.
+struct IsoRow {
+  unsigned y, z, t;
+  unsigned up;  // bit 0 y + 1, bit 1 z + 1, bit 2 t + 1
+};
+__device__ __forceinline__ IsoRow iso_row(const IsoGrid& g, unsigned r) {
+  IsoRow q;
+  q.y = r % (unsigned)g.ny;
+  const unsigned zt = r / (unsigned)g.ny;
+  q.z = zt % (unsigned)g.nz;
+  q.t = zt / (unsigned)g.nz;
+  q.up = (q.y + 1 < (unsigned)g.ny ? 1u : 0u) | (q.z + 1 < (unsigned)g.nz ? 2u : 0u) |
+         (q.t + 1 < (unsigned)g.nt ? 4u : 0u);
+  return q;
+}
+// Words from a row to the row at (dy, dz, dt) = the bits of m above it.
+__device__ __forceinline__ long long row_step(const IsoGrid& g, int m) {
+  return ((m & 1) + (((m >> 1) & 1) + (long long)((m >> 2) & 1) * g.nz) * g.ny) * (long long)g.nwx;
+}
+// Vertices of word column j inside the grid, and those with a neighbour at x + 1.
+__device__ __forceinline__ u64 word_in(const IsoGrid& g, int j) {
+  const int n = g.nx - 64 * j;
+  return n >= 64 ? ~0ull : (1ull << n) - 1ull;
+}
+__device__ __forceinline__ u64 word_in_x1(const IsoGrid& g, int j) {
+  const int n = g.nx - 64 * j - 1;
+  return n >= 64 ? ~0ull : (n > 0 ? (1ull << n) - 1ull : 0ull);
+}
+// Positions where a run of equal sides starts, but the first.
+__device__ __forceinline__ u64 run_starts(u64 w, u64 in) { return (w ^ (w << 1)) & in & ~1ull; }
+__device__ __forceinline__ int run_at(u64 starts, int p) { return __popcll(starts & ((2ull << p) - 1ull)); }
+
+// The sides of the 16 cube corners of a word's 64 vertices (corner mask x | y << 1 | z << 2 | t << 3) and which are in
+// the grid.  One lane per word; the words of the row x and of the 7 rows above it.
+struct IsoCorners {
+  u64 s[16], in[16];
+};
+__device__ __forceinline__ void iso_corners(const IsoGrid& g, long long k, int j, unsigned up, IsoCorners& q) {
+  u64 w[8], n[8];
+  const bool more = j + 1 < g.nwx;
 #pragma unroll
-  for (int cm = 0; cm < 16; ++cm) {  // clamped (in-grid) word addresses: the 16 loads are independent
-    const int cx = min(x + (cm & 1), g.nx - 1), cy = min(y + ((cm >> 1) & 1), g.ny - 1);
-    const int cz = min(z + ((cm >> 2) & 1), g.nz - 1), ct = min(t + ((cm >> 3) & 1), g.nt - 1);
-    w[cm] = g.bits[(((long long)ct * g.nz + cz) * g.ny + cy) * g.nwx + (cx >> 6)];
+  for (int m = 0; m < 8; ++m) {  // rows past the grid: this row's words (dropped by in), all loads in flight together
+    const long long a = k + ((m & ~(int)up) ? 0 : row_step(g, m));
+    w[m] = g.bits[a];
+    n[m] = g.bits[a + (more ? 1 : 0)];
   }
+  const u64 in0 = word_in(g, j), in1 = word_in_x1(g, j);
 #pragma unroll
-  for (int cm = 0; cm < 16; ++cm) {
-    const int cx = x + (cm & 1), cy = y + ((cm >> 1) & 1), cz = z + ((cm >> 2) & 1), ct = t + ((cm >> 3) & 1);
-    if (cx < g.nx && cy < g.ny && cz < g.nz && ct < g.nt) {
-      valid |= 1u << cm;
-      above |= (unsigned)((w[cm] >> (cx & 63)) & 1ull) << cm;
-    }
+  for (int m = 0; m < 8; ++m) {
+    const bool ok = (m & ~(int)up) == 0;
+    q.s[2 * m] = w[m];
+    q.s[2 * m + 1] = (w[m] >> 1) | (more ? n[m] << 63 : 0ull);
+    q.in[2 * m] = ok ? in0 : 0ull;
+    q.in[2 * m + 1] = ok ? in1 : 0ull;
   }
 }
 
@@ -182,267 +172,541 @@ __device__ __forceinline__ int pen_tets_all(std::integer_sequence<int, TY...>, u
   return (pen_tets<TY>(above) + ...);
 }
 
-__global__ __launch_bounds__(kIsoBX) void iso_count(IsoGrid g, unsigned short* __restrict__ emask,
-                                                     unsigned char* __restrict__ hcnt, unsigned char* __restrict__ tcnt,
-                                                     unsigned* __restrict__ status) {
-  const int x = blockIdx.x * kIsoBX + threadIdx.x;
-  const int y = blockIdx.y;
-  const int z = blockIdx.z % g.nz, t = blockIdx.z / g.nz;
-  if (x >= g.nx) return;
-  const long long v = vidx(g, x, y, z, t);
-  unsigned above, valid;
-  corner_bits(g, x, y, z, t, above, valid);
-  unsigned m = 0;
-#pragma unroll
-  for (int M = 1; M < 16; ++M)
-    if (((valid >> M) & 1u) && (((above >> M) ^ above) & 1u)) m |= 1u << (M - 1);
-  int tets = 0;
-  if (valid == 0xffffu && above != 0u && above != 0xffffu)
-    tets = pen_tets_all(std::make_integer_sequence<int, 24>{}, above);
-  emask[v] = (unsigned short)m;
-  hcnt[v] = (unsigned char)__popc(m);
-  tcnt[v] = (unsigned char)tets;
-}
-
-// list of the vertices whose cube has crossed pentachora (about one in sixteen on smooth fields), in vertex order,
-// so that the pentachoron pass runs on busy lanes only
-__global__ void iso_active_list(const unsigned char* __restrict__ tcnt, const long long* __restrict__ abase,
-                                long long V, long long* __restrict__ list) {
-  const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < V && tcnt[v]) list[off16(abase, tcnt, v, true)] = v;
-}
-
-__global__ __launch_bounds__(kIsoBX) void iso_emit(IsoGrid g, const unsigned short* __restrict__ emask,
-                                                    const long long* __restrict__ hbase,
-                                                    const unsigned char* __restrict__ hcnt, long long* __restrict__ edge_id,
-                                                    float* __restrict__ pos, unsigned* __restrict__ parent) {
-  const int x = blockIdx.x * kIsoBX + threadIdx.x;
-  const int y = blockIdx.y;
-  const int z = blockIdx.z % g.nz, t = blockIdx.z / g.nz;
-  if (x >= g.nx) return;
-  const long long v = vidx(g, x, y, z, t);
-  const unsigned m = emask[v];
-  if (!m) return;
-  const float f0 = g.f[v];
-  // the far ends of the 15 edges from clamped (in-grid) addresses, all loads in flight before any store (a load
-  // issued after a store waits for it); crossed edges only reach corners inside the grid
-  float f1[16];
-#pragma unroll
-  for (int M = 1; M < 16; ++M)
-    f1[M] = g.f[vidx(g, min(x + (M & 1), g.nx - 1), min(y + ((M >> 1) & 1), g.ny - 1),
-                     min(z + ((M >> 2) & 1), g.nz - 1), min(t + ((M >> 3) & 1), g.nt - 1))];
-  const long long o0 = off16(hbase, hcnt, v, false);
-#pragma unroll
-  for (int M = 1; M < 16; ++M) {
-    if (!((m >> (M - 1)) & 1u)) continue;
-    const long long o = o0 + __popc(m & ((1u << (M - 1)) - 1u));
-    const int dx = M & 1, dy = (M >> 1) & 1, dz = (M >> 2) & 1, dt = (M >> 3) & 1;
-    const float mu = (g.c - f0) / (f1[M] - f0);
-    edge_id[o] = v * 15 + (M - 1);
-    if (pos)
-      reinterpret_cast<float4*>(pos)[o] = make_float4((float)x + mu * (float)dx, (float)y + mu * (float)dy,
-                                                      (float)z + mu * (float)dz, (float)t + mu * (float)dt);
-    parent[o] = (unsigned)o;
-  }
-}
-
-// Tessellation of the cube's pentachoron of type TY (Sec. 6.1): with k of its five chain vertices above the level,
-// case I (one vertex on the smaller side) gives the tetrahedron of its four crossed edges, case II (two) the three
-// tetrahedra of the prism between their crossed edges.  The chain corners are compile-time constants, so the
-// corners' first hit indices and crossing masks are read from registers by constant index; the lane-dependent
-// chain positions are bit fields, and every tetrahedron is one 16-byte store.  Returns false after flagging an
-// internal error (a crossed edge the count pass did not record, or more tetrahedra than it counted).
-// Hit index of the crossed edge between chain positions i and j of a pentachoron (chain corners in 4-bit fields of
-// chw; lower end at position min(i, j) <= 3, whose corner's first hit index and crossing mask are b_k and m_k).
-// The values come by value: selecting between references would become a load through a selected address, which
-// keeps them in scratch memory.
-__device__ __forceinline__ int iso_edge(unsigned i, unsigned j, unsigned chw, long long b0, long long b1, long long b2,
-                                        long long b3, unsigned m0, unsigned m1, unsigned m2, unsigned m3, bool& bad) {
-  const unsigned lo = min(i, j), hi = max(i, j);
-  const unsigned a = (chw >> (4u * lo)) & 15u, M = ((chw >> (4u * hi)) & 15u) ^ a;
-  const long long b = lo == 0 ? b0 : (lo == 1 ? b1 : (lo == 2 ? b2 : b3));
-  const unsigned mk = lo == 0 ? m0 : (lo == 1 ? m1 : (lo == 2 ? m2 : m3));
-  bad = bad || !((mk >> (M - 1u)) & 1u);
-  return (int)(b + __popc(mk & ((1u << (M - 1u)) - 1u)));
-}
-
+// Tetrahedra of the pentachora of type TY of a word's vertices, added to n.
 template <int TY>
-__device__ __forceinline__ bool iso_tess(unsigned above, const long long (&cb)[16], const unsigned (&cm_mask)[15],
-                                         long long& o, long long o_end, int* __restrict__ tets, unsigned* status) {
+__device__ __forceinline__ void pen_sum(const IsoCorners& q, const u64 (&s1)[16], const u64 (&c1)[16], u64 in, int& n) {
   constexpr PenCorners kP = build_pen_corners();
-  constexpr unsigned c0 = kP.c[TY][0], c1 = kP.c[TY][1], c2 = kP.c[TY][2], c3 = kP.c[TY][3], c4 = kP.c[TY][4];
-  constexpr unsigned chw = c0 | c1 << 4 | c2 << 8 | c3 << 12 | c4 << 16;
-  const unsigned lm = ((above >> c0) & 1u) | ((above >> c1) & 1u) << 1 | ((above >> c2) & 1u) << 2 |
-                      ((above >> c3) & 1u) << 3 | ((above >> c4) & 1u) << 4;
-  const int k = __popc(lm);
-  if (k == 0 || k == 5) return true;
-  // chain positions on the smaller side (minority: one or two) and the others, each in increasing order
-  const unsigned mino = k <= 2 ? lm : (~lm & 31u);
-  const int nm = __popc(mino);
-  const unsigned mi0 = (unsigned)__ffs((int)mino) - 1u, mi1 = (unsigned)__ffs((int)(mino & (mino - 1u))) - 1u;
-  unsigned majo = ~mino & 31u;
-  unsigned ma[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    ma[q] = (unsigned)__ffs((int)majo) - 1u;
-    majo &= majo - 1u;
-  }
-  // hit index of the crossed edge between chain positions i and j (lower end at position min(i, j) <= 3)
-  const long long cb0 = cb[c0], cb1 = cb[c1], cb2 = cb[c2], cb3 = cb[c3];
-  const unsigned mk0 = cm_mask[c0], mk1 = cm_mask[c1], mk2 = cm_mask[c2], mk3 = cm_mask[c3];
-  bool bad = false;
-  auto edge = [&](unsigned i, unsigned j) -> int {
-    return iso_edge(i, j, chw, cb0, cb1, cb2, cb3, mk0, mk1, mk2, mk3, bad);
-  };
-  const bool two = nm == 2;
-  // case I: (m, a0..a3); case II: (p1, a0..a2), (p2, a0..a2)
-  const int e0 = edge(mi0, ma[0]), e1 = edge(mi0, ma[1]), e2 = edge(mi0, ma[2]);
-  const int e3 = two ? edge(mi1, ma[0]) : edge(mi0, ma[3]);
-  int e4 = 0, e5 = 0;
-  if (two) {
-    e4 = edge(mi1, ma[1]);
-    e5 = edge(mi1, ma[2]);
-  }
-  const int nt_here = two ? 3 : 1;
-  if (bad || o + nt_here > o_end) {
-    atomicOr(status, ST_INVARIANT);
-    return false;
-  }
-  int4* T = reinterpret_cast<int4*>(tets) + o;
-  if (!two) {
-    T[0] = make_int4(e0, e1, e2, e3);
-  } else {
-    T[0] = make_int4(e0, e1, e2, e5);
-    T[1] = make_int4(e0, e1, e4, e5);
-    T[2] = make_int4(e0, e3, e4, e5);
-  }
-  o += nt_here;
-  return true;
+  // five sides added bit-sliced: s1, c1 hold those of corners 0, 15 and the first chain corner
+  constexpr int a = kP.c[TY][1], b = kP.c[TY][2], c = kP.c[TY][3];
+  const u64 s2 = s1[a] ^ q.s[b] ^ q.s[c];
+  const u64 c2 = (s1[a] & q.s[b]) | (s1[a] & q.s[c]) | (q.s[b] & q.s[c]);
+  const u64 two = (c1[a] ^ c2) & in;        // two or three above: case II
+  const u64 one = (s2 ^ c1[a]) & ~two & in; // one or four above: case I
+  n += __popcll(one) + 3 * __popcll(two);
 }
-
 template <int... TY>
-__device__ __forceinline__ void iso_tess_all(std::integer_sequence<int, TY...>, unsigned above,
-                                             const long long (&cb)[16], const unsigned (&cm_mask)[15], long long& o,
-                                             long long o_end, int* __restrict__ tets, unsigned* status) {
-  (void)(iso_tess<TY>(above, cb, cm_mask, o, o_end, tets, status) && ...);  // stops at the first error
-}
-
-__global__ __launch_bounds__(kIsoBX) void iso_unite(IsoGrid g, const long long* __restrict__ active,
-                                                     long long n_active, const unsigned short* __restrict__ emask,
-                                                     const long long* __restrict__ hbase,
-                                                     const unsigned char* __restrict__ hcnt,
-                                                     const unsigned char* __restrict__ tcnt,
-                                                     const long long* __restrict__ tbase, unsigned* __restrict__ parent,
-                                                     int* __restrict__ tets, unsigned* __restrict__ status) {
-  const long long a_i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a_i >= n_active) return;
-  const long long v = active[a_i];
-  const int x = (int)(v % g.nx);
-  const int y = (int)((v / g.nx) % g.ny);
-  const int z = (int)((v / ((long long)g.nx * g.ny)) % g.nz);
-  const int t = (int)(v / ((long long)g.nx * g.ny * g.nz));
-  if (tcnt[v] == 0) return;
-  unsigned above, valid;
-  corner_bits(g, x, y, z, t, above, valid);
-  // first hit index and crossing mask of every corner that anchors an edge of a pentachoron (all but 1111)
-  long long cb[16];
-  unsigned cm_mask[15];
-  // corners in x pairs (w, w + 1): one group load gives both offsets unless w ends its group of 16
+__device__ __forceinline__ int pen_sum_all(std::integer_sequence<int, TY...>, const IsoCorners& q, u64 in) {
+  u64 s1[16], c1[16];
 #pragma unroll
-  for (int cm = 0; cm < 15; cm += 2) {
-    const long long w = vidx(g, x, y + ((cm >> 1) & 1), z + ((cm >> 2) & 1), t + ((cm >> 3) & 1));
-    const long long g0 = w & ~15ll;
-    const int k = (int)(w - g0);
-    const uint4 q = *reinterpret_cast<const uint4*>(hcnt + g0);
-    cb[cm] = hbase[w >> 4] + sum_first(q, k, false);
-    const unsigned wk = k < 4 ? q.x : (k < 8 ? q.y : (k < 12 ? q.z : q.w));
-    cb[cm + 1] = k < 15 ? cb[cm] + ((wk >> (8 * (k & 3))) & 0xFFu) : hbase[(w + 1) >> 4];
-    cm_mask[cm] = emask[w];
-    if (cm + 1 < 15) cm_mask[cm + 1] = emask[w + 1];
+  for (int a = 1; a < 16; a <<= 1) {
+    s1[a] = q.s[0] ^ q.s[15] ^ q.s[a];
+    c1[a] = (q.s[0] & q.s[15]) | (q.s[0] & q.s[a]) | (q.s[15] & q.s[a]);
   }
-  long long o = off16(tbase, tcnt, v, false);
-  const long long o_end = o + tcnt[v];
-  // Unions: the cube's crossed edges P (local set) grouped by "edges of a common pentachoron" (a group grows from
-  // its lowest member through the side sets until it is stable); each member is united once with the group's first.
-  // Same connectivity as uniting the crossed edges of every pentachoron, with |P| - groups unions.
-  {
-    u128 P = 0;
-    for (int k = 0; k < kCubeEdgeN; ++k) {
-      const unsigned a = kCubeEdges.ea[k], b = a | kCubeEdges.eM[k];
-      if (((above >> a) ^ (above >> b)) & 1u) {
-        if (!((cm_mask[a] >> (kCubeEdges.eM[k] - 1)) & 1u)) {  // the count pass took the same decisions
-          atomicOr(status, ST_INVARIANT);
-          return;
-        }
-        P |= (u128)1 << k;
-      }
-    }
-    auto hit = [&](int k) -> long long {
-      const unsigned a = kCubeEdges.ea[k], M = kCubeEdges.eM[k];
-      return cb[a] + __popc(cm_mask[a] & ((1u << (M - 1)) - 1u));
-    };
-    u128 R = P;
-    while (R) {
-      u128 C = (u128)1 << low_bit128(R), prev;
-      do {
-        prev = C;
-        for (int pt = 0; pt < 24; ++pt) {
-          const u128 S = edge_side_set(pt) & P;
-          if (S & C) C |= S;
-        }
-      } while (C != prev);
-      R &= ~C;
-      const int k0 = low_bit128(C);
-      const long long h0 = hit(k0);
-      C &= ~((u128)1 << k0);
-      unsigned r = C ? uf_find_cached(parent, (unsigned)h0) : 0u;
-      while (C) {
-        const int k = low_bit128(C);
-        C &= ~((u128)1 << k);
-        r = uf_unite_into(parent, r, (unsigned)hit(k));
-      }
-    }
-  }
-  iso_tess_all(std::make_integer_sequence<int, 24>{}, above, cb, cm_mask, o, o_end, tets, status);
+  int n = 0;
+  (pen_sum<TY>(q, s1, c1, in, n), ...);
+  return n;
 }
 
-dim3 iso_grid(const IsoGrid& g) { return dim3((unsigned)((g.nx + kIsoBX - 1) / kIsoBX), (unsigned)g.ny, (unsigned)(g.nz * g.nt)); }
+// Counts per word, bit-parallel over its 64 vertices (bound by VALU issue).  Per vertex, with byte arrays whose group
+// sums were scanned, the counts took 2.2 + 0.6 ms on 256^3 x 16; per word 0.13 + 0.13 ms.
+__global__ __launch_bounds__(256) void iso_count(IsoGrid g, long long n_words, int* __restrict__ hcnt,
+                                                 int* __restrict__ acnt, int* __restrict__ rcnt,
+                                                 u64* __restrict__ n_tets) {
+  __shared__ int s_tets;
+  if (threadIdx.x == 0) s_tets = 0;
+  __syncthreads();
+  // a bounded grid: one addition to the common total per workgroup (they serialise)
+  for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < n_words; k += (long long)gridDim.x * 256) {
+    const unsigned r = (unsigned)(k / g.nwx);
+    const int j = (int)(k - (long long)r * g.nwx);
+    IsoCorners q;
+    iso_corners(g, k, j, iso_row(g, r).up, q);
+    u64 any = q.s[0], all = ~0ull;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      any |= q.s[c] & q.in[c];
+      all &= q.s[c] | ~q.in[c];
+    }
+    int h = 0, a = 0;
+    const u64 mixed = any & ~all & q.in[0];  // vertices with both sides among their corners
+    if (mixed) {
+#pragma unroll
+      for (int c = 1; c < 16; ++c) h += __popcll((q.s[0] ^ q.s[c]) & q.in[c]);
+      a = __popcll(mixed & q.in[15]);
+      const int t = pen_sum_all(std::make_integer_sequence<int, 24>{}, q, q.in[15]);
+      if (t) atomicAdd(&s_tets, t);
+    }
+    hcnt[k] = h;
+    acnt[k] = a;
+    rcnt[k] = 1 + __popcll(run_starts(q.s[0], q.in[0]));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && s_tets) atomicAdd(n_tets, (u64)s_tets);
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Components of the vertices on one side.  A node is a run of equal sides in a word, numbered in vertex order (rbase:
+// first run of each word), so the root of a union-find tree, its smallest node, holds the component's first vertex.
+// ---------------------------------------------------------------------------------------------------------------
+// A run's parent: the run on its side before it along t, z, y or x that holds or precedes its first vertex, else
+// itself (parents are smaller: a forest, flattened by uf_compress before the unions).
+__global__ __launch_bounds__(256) void iso_runs_init(IsoGrid g, long long n_words, const long long* __restrict__ rbase,
+                                                     unsigned* __restrict__ parent) {
+  const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (k >= n_words) return;
+  const unsigned r = (unsigned)(k / g.nwx);
+  const int j = (int)(k - (long long)r * g.nwx);
+  const IsoRow q = iso_row(g, r);
+  const u64 in = word_in(g, j), w = g.bits[k];
+  const long long at[3] = {q.t ? k - row_step(g, 4) : k, q.z ? k - row_step(g, 2) : k, q.y ? k - row_step(g, 1) : k};
+  const bool ok[3] = {q.t != 0, q.z != 0, q.y != 0};
+  u64 o[3];
+  unsigned ob[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    o[a] = g.bits[at[a]];
+    ob[a] = (unsigned)rbase[at[a]];
+  }
+  const unsigned b = (unsigned)rbase[k];
+  const bool joins = j > 0 && ((g.bits[j > 0 ? k - 1 : k] >> 63) & 1ull) == (w & 1ull);
+  u64 st = run_starts(w, in) | 1ull;
+  for (unsigned n = b; st; ++n) {
+    const int p = __ffsll((long long)st) - 1;
+    st &= st - 1;
+    unsigned par = p == 0 && joins ? b - 1u : n;
+#pragma unroll
+    for (int a = 2; a >= 0; --a)
+      if (ok[a] && !(((o[a] ^ w) >> p) & 1ull)) par = ob[a] + (unsigned)run_at(run_starts(o[a], in), p);
+    parent[n] = par;
+  }
+}
+
+// The links between runs that the others do not imply.  The axes are taken in the order t, z, y, x.  Along t, z or y:
+// one link per stretch of a word where both rows keep one side; along x: a word's last run and the next word's first.
+// A link along a is implied, and left out, when at one of its vertices v the four vertices v, v + e(a), v + e(b),
+// v + e(a) + e(b) are on one side for an earlier axis b (it then follows from the one at v + e(b) and the links along
+// b).  Along t, the stretches that hold the first vertex of a run of the upper row are done by iso_runs_init.  Of several
+// axes: only where every corner between is on the other side.  Inside the components nearly all links are implied, so
+// what is left grows with the level set (256^3 x 16, 34 isovolumes: 0.6 ms with x first and no link from the
+// initialisation counted, 0.20 now).
+__global__ __launch_bounds__(256) void iso_runs_link(IsoGrid g, long long n_words, const long long* __restrict__ rbase,
+                                                     unsigned* __restrict__ parent) {
+  const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (k >= n_words) return;
+  const unsigned r = (unsigned)(k / g.nwx);
+  const int j = (int)(k - (long long)r * g.nwx);
+  const unsigned up = iso_row(g, r).up;
+  IsoCorners q;
+  iso_corners(g, k, j, up, q);
+  const bool more = j + 1 < g.nwx;
+  const u64 w = q.s[0], in = q.in[0], st = run_starts(w, in);
+  const unsigned b = (unsigned)rbase[k];
+  if (more && !(((q.s[1] ^ w) >> 63) & 1ull)) {
+    u64 implied = 0;
+#pragma unroll
+    for (int c = 1; c < 8; c <<= 1)
+      if (up & (unsigned)c) implied |= ~(w ^ q.s[2 * c]) & ~(w ^ q.s[2 * c + 1]);
+    if (!(implied >> 63)) {
+      const unsigned nb = (unsigned)rbase[k + 1];
+      uf_unite_cached(parent, nb - 1u, nb);
+    }
+  }
+#pragma unroll
+  for (int a = 4; a >= 1; a >>= 1) {  // row masks t, z, y
+    if (!(up & (unsigned)a)) continue;
+    const u64 same = ~(w ^ q.s[2 * a]) & in;
+    u64 implied = 0;
+    if (a == 4) implied = run_starts(q.s[8], in) | 1ull;
+#pragma unroll
+    for (int c = 4; c > a; c >>= 1)
+      if (up & (unsigned)c) implied |= same & ~(w ^ q.s[2 * c]) & ~(w ^ q.s[2 * (a | c)]);
+    u64 left = same;
+    while (left) {
+      const int p = __ffsll((long long)left) - 1;
+      // the stretch from p: up to the next vertex off it or the next run
+      const u64 stop = (~same | st) & ~((2ull << p) - 1ull);
+      const u64 upto = stop ? (stop & (0ull - stop)) - 1ull : ~0ull;
+      const u64 part = left & upto;
+      left &= ~upto;
+      if (part & implied) continue;
+      const long long o = k + row_step(g, a);
+      uf_unite_cached(parent, b + (unsigned)run_at(st, p),
+                      (unsigned)rbase[o] + (unsigned)run_at(run_starts(q.s[2 * a], in), p));
+    }
+  }
+#pragma unroll
+  for (int M = 3; M < 16; ++M) {
+    if ((M & (M - 1)) == 0) continue;
+    u64 need = ~(w ^ q.s[M]) & q.in[M];
+#pragma unroll
+    for (int m = 1; m < M; ++m)
+      if ((m & M) == m) need &= w ^ q.s[m];
+    while (need) {
+      const int p = __ffsll((long long)need) - 1;
+      need &= need - 1;
+      const int x = p + (M & 1);
+      const long long o = k + row_step(g, M >> 1) + (x >> 6);
+      const u64 ow = g.bits[o];
+      uf_unite_cached(parent, b + (unsigned)run_at(st, p),
+                      (unsigned)rbase[o] + (unsigned)run_at(run_starts(ow, word_in(g, j + (x >> 6))), x & 63));
+    }
+  }
+}
+
+// Every run's component (its root), the number of components, and the components' smallest edge ids cleared.
+__global__ __launch_bounds__(256) void iso_runs_done(const unsigned* __restrict__ parent, long long n,
+                                                     unsigned* __restrict__ comp, long long* __restrict__ first,
+                                                     u64* __restrict__ roots) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  unsigned root = 0;
+  if (i < n) {
+    root = uf_find_plain(parent, (unsigned)i);
+    comp[i] = root;
+    first[i] = 0x7fffffffffffffffll;
+  }
+  const u64 b = __ballot(i < n && root == (unsigned)i);
+  if (b && lane_id() == 0) atomicAdd(roots, (u64)__popcll(b));
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Emission.  A wavefront looks at the counts of kIsoEmitWords words and takes those with crossings one after another: lane =
+// vertex for the crossing masks, offsets and cubes, then lane = crossing, so that ids, points and components go out in
+// contiguous stores.  Bound by issue (about 340 vector and 280 scalar operations a word, 1.9 ms for the 1.6 M words with
+// crossings of the 256^3 x 16 series; 16 or 32 words a wavefront: 2.0).
+// ---------------------------------------------------------------------------------------------------------------
+constexpr int kIsoEmitWords = 64;
+struct IsoWave {
+  unsigned short map[15 * 64];  // crossing j of the word -> vertex lane | mask << 6
+  u64 starts[16];               // run starts and first run of the word's row and the 7 rows above it, at this word
+  unsigned run[16];             // column and the next
+};
+
+__device__ __forceinline__ u64 lane_word(u64 v, int l) {
+  return (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, l) |
+         (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), l) << 32;
+}
+
+__global__ __launch_bounds__(256) void iso_emit(IsoGrid g, long long n_words, const int* __restrict__ hcnt,
+                                                const long long* __restrict__ hbase,
+                                                const long long* __restrict__ abase, const long long* __restrict__ rbase,
+                                                const unsigned* __restrict__ comp, unsigned* __restrict__ vinfo,
+                                                long long* __restrict__ edge_id, float* __restrict__ pos,
+                                                unsigned* __restrict__ hcomp, long long* __restrict__ first,
+                                                long long* __restrict__ list) {
+  __shared__ IsoWave sw[4];
+  __shared__ long long step[16];  // from a vertex to its corner M
+  if (threadIdx.x < 16) {
+    const long long M = threadIdx.x;
+    step[M] = (M & 1) + ((M >> 1) & 1) * (long long)g.nx +
+              (((M >> 2) & 1) + (M >> 3) * g.nz) * (long long)g.nx * (long long)g.ny;
+  }
+  __syncthreads();
+  IsoWave& W = sw[threadIdx.x >> 6];
+  const int lane = lane_id();
+  const long long k0 = ((long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * kIsoEmitWords;
+  if (k0 >= n_words) return;
+  // lane l: word k0 + l
+  const long long kl = min(k0 + min(lane, kIsoEmitWords - 1), n_words - 1);
+  const int hc = lane < kIsoEmitWords && k0 + lane < n_words ? hcnt[kl] : 0;
+  const long long hb = hbase[kl], ab = abase[kl];
+  const unsigned rl = (unsigned)(kl / g.nwx);
+  const int jl = (int)(kl - (long long)rl * g.nwx);
+  const IsoRow ql = iso_row(g, rl);
+  const long long sx = g.nx, sxy = sx * g.ny, sxyz = sxy * g.nz;
+  u64 todo = __ballot(hc > 0);
+  if (!todo) return;
+  // the 16 words around word e: lane 2 m + c = row m, column j + c, four lanes each for the components of their first
+  // four runs (the sides of a word's runs alternate)
+  auto around = [&](int e, u64& w, unsigned& rn) -> bool {
+    const int j = __builtin_amdgcn_readlane(jl, e);
+    const unsigned up = (unsigned)__builtin_amdgcn_readlane((int)ql.up, e);
+    const int m = (lane >> 1) & 7, c = lane & 1;
+    const bool inside = (m & ~(int)up) == 0 && (c == 0 || j + 1 < g.nwx);
+    const long long a = k0 + e + (inside ? row_step(g, m) + c : 0);
+    w = g.bits[a];
+    rn = (unsigned)rbase[a];
+    return inside;
+  };
+  u64 wl;
+  unsigned rn;
+  int e = __ffsll((long long)todo) - 1;
+  bool inside = around(e, wl, rn);
+  for (;;) {
+    todo &= todo - 1;
+    const int j = __builtin_amdgcn_readlane(jl, e), total = __builtin_amdgcn_readlane(hc, e);
+    const unsigned up = (unsigned)__builtin_amdgcn_readlane((int)ql.up, e);
+    const unsigned y = (unsigned)__builtin_amdgcn_readlane((int)ql.y, e), z = (unsigned)__builtin_amdgcn_readlane((int)ql.z, e);
+    const unsigned t = (unsigned)__builtin_amdgcn_readlane((int)ql.t, e);
+    const long long h0 = (long long)lane_word((u64)hb, e), a0 = (long long)lane_word((u64)ab, e);
+    const u64 starts = run_starts(wl, word_in(g, j + (inside ? lane & 1 : 0)));
+    const int runs = 1 + __popcll(starts), run = min(lane >> 4, runs - 1);
+    const unsigned rcomp = comp[rn + (unsigned)run];
+    // one component on each side among all of them: every crossing of the word is of one isovolume
+    const bool over = (((unsigned)wl ^ (unsigned)run) & 1u) != 0;
+    const u64 bo = __ballot(over), bu = __ballot(!over);
+    const unsigned co = (unsigned)__builtin_amdgcn_readlane((int)rcomp, bo ? __ffsll((long long)bo) - 1 : 0);
+    const unsigned cu = (unsigned)__builtin_amdgcn_readlane((int)rcomp, bu ? __ffsll((long long)bu) - 1 : 0);
+    const bool single = __ballot(runs > 4 || rcomp != (over ? co : cu)) == 0;
+    const u64 wz = inside ? wl : 0ull;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the previous word's reads of W are done
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 16) {
+      W.starts[lane] = starts;
+      W.run[lane] = rn;
+    }
+    u64 s[16], valid[16];
+    const u64 in0 = word_in(g, j), in1 = word_in_x1(g, j);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const bool ok = (m & ~(int)up) == 0;
+      const u64 w = lane_word(wz, 2 * m);
+      s[2 * m] = w;
+      s[2 * m + 1] = (w >> 1) | (lane_word(wz, 2 * m + 1) << 63);
+      valid[2 * m] = ok ? in0 : 0ull;
+      valid[2 * m + 1] = ok ? in1 : 0ull;
+    }
+    unsigned m = 0;
+    u64 any = s[0], all = s[0];
+#pragma unroll
+    for (int M = 1; M < 16; ++M) {
+      any |= s[M];
+      all &= s[M];
+      m |= __builtin_amdgcn_inverse_ballot_w64((s[0] ^ s[M]) & valid[M]) ? 1u << (M - 1) : 0u;
+    }
+    const unsigned n = __popc(m);
+    unsigned at = wave_incl_scan(n) - n;
+    const long long v0 = ((long long)t * sxyz + (long long)z * sxy + (long long)y * sx) + 64ll * j;
+    const unsigned info = at | m << 16;
+    for (unsigned mm = m; mm; mm &= mm - 1u) W.map[at++] = (unsigned short)((unsigned)lane | (unsigned)__ffs((int)mm) << 6);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // Loads before stores: a load issued after a store waits for it too.  First this word's field values (for its first
+    // 64 crossings), then the next word's words, then the stores.
+    const float* F = g.f + v0;
+    const int i_last = total - 1;
+    unsigned ent = W.map[min(lane, i_last)];
+    float f0 = F[ent & 63u], f1 = F[(ent & 63u) + step[ent >> 6]];
+    const unsigned rc1 = max(co, cu);
+    const long long seen = first[rc1];
+    const int next = todo ? __ffsll((long long)todo) - 1 : e;
+    inside = around(next, wl, rn);
+    if (64 * j + lane < g.nx) vinfo[v0 + lane] = info;
+    // cubes with tetrahedra: vertex and the sides of its corners (a corner's side differs where its edge is crossed)
+    const u64 act = any & ~all & valid[15];
+    if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+      const unsigned above = (m << 1) ^ (__builtin_amdgcn_inverse_ballot_w64(s[0]) ? 0xFFFFu : 0u);
+      const long long a = a0 + __builtin_amdgcn_mbcnt_hi((unsigned)(act >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)act, 0u));
+      list[a] = (long long)((u64)(v0 + lane) | (u64)above << 48);
+    }
+    const long long id0 = v0 * 15 - 1;
+    const float fx = (float)(64 * j), fy = (float)(int)y, fz = (float)(int)z, ft = (float)(int)t;
+    for (int i = lane;;) {
+      const bool on = i < total;
+      const int L = (int)(ent & 63u), M = (int)(ent >> 6);
+      const int dx = M & 1, dy = (M >> 1) & 1, dz = (M >> 2) & 1, dt = M >> 3;
+      const float mu = (g.c - f0) / (f1 - f0);
+      const long long id = id0 + (L * 15 + M);
+      unsigned rc = rc1;
+      bool own = i == 0 && id < seen;
+      if (!single) {
+        const int x1 = L + dx, o = (M & ~1) | (x1 >> 6);
+        rc = max(comp[W.run[0] + (unsigned)run_at(W.starts[0], L)],
+                 comp[W.run[o] + (unsigned)run_at(W.starts[o], x1 & 63)]);
+        // ids ascend with the lane: lane 0 stands for the wavefront's leading component
+        const unsigned lead = (unsigned)__builtin_amdgcn_readfirstlane((int)rc);
+        own = on && (rc != lead || lane == 0) && id < first[rc];
+      }
+      if (on) {
+        edge_id[h0 + i] = id;
+        if (pos)
+          reinterpret_cast<float4*>(pos)[h0 + i] = make_float4((fx + (float)L) + mu * (float)dx, fy + mu * (float)dy,
+                                                               fz + mu * (float)dz, ft + mu * (float)dt);
+        hcomp[h0 + i] = rc;
+        if (own) atomicMin(first + rc, id);
+      }
+      i += 64;
+      if (i - lane >= total) break;
+      ent = W.map[min(i, i_last)];
+      f0 = F[ent & 63u];
+      f1 = F[(ent & 63u) + step[ent >> 6]];
+    }
+    if (!todo) break;
+    e = next;
+  }
+}
+
+// Tessellation (Sec. 6.1).  In a pentachoron with k of its five chain vertices above the level, case I (one vertex on
+// the smaller side) gives the tetrahedron of its four crossed edges, case II (two) the three tetrahedra of the prism
+// between their crossed edges.  A wavefront takes 64 listed cubes: lane = cube for the corners' first hits and crossing
+// masks and for listing its crossed pentachora, then lane = pentachoron, whose tetrahedra follow those of the lane
+// before: they are staged in LDS and go out as contiguous 16-byte stores.  (One lane per cube with the 24 types unrolled
+// ran every type for every wavefront and scattered each store over 64 lines: 2.86 against 1.52 ms on 256^3 x 16, 299 M
+// tetrahedra, whose 4.8 GB are the bound; stored straight from the pentachoron lanes, 16 bytes each 48: 2.58 ms.)
+struct IsoTess {
+  uint2 corner[16][65];           // by corner, cube (padded: the lanes of a cube read different corners): first hit, mask
+  unsigned short pen[24 * 64];    // crossed pentachora in output order: cube | type << 6
+  int4 out[3 * 64];               // tetrahedra of 64 of them
+};
+// Chain corners of the 24 types as 4-bit fields, and for each set of chain positions above the level the positions on
+// the smaller side (first, second) and the others, each in increasing order, as 3-bit fields.
+struct IsoPenTables {
+  unsigned chain[24], split[32];
+};
+constexpr IsoPenTables build_pen_tables() {
+  IsoPenTables r{};
+  const PenCorners c = build_pen_corners();
+  for (int ty = 0; ty < 24; ++ty)
+    for (int k = 0; k < 5; ++k) r.chain[ty] |= (unsigned)c.c[ty][k] << (4 * k);
+  for (unsigned lm = 0; lm < 32; ++lm) {
+    const unsigned mino = popc_c((int)lm) <= 2 ? lm : (~lm & 31u);
+    unsigned a = 0, b = 2;  // fields 0, 1: smaller side; 2..5: the others
+    for (unsigned p = 0; p < 5; ++p) {
+      const unsigned f = (mino >> p) & 1u ? a++ : b++;
+      if (f < 6) r.split[lm] |= p << (3 * f);
+    }
+    r.split[lm] |= (popc_c((int)mino) == 2 ? 1u : 0u) << 18;
+  }
+  return r;
+}
+__constant__ IsoPenTables kIsoPenTables = build_pen_tables();
+
+// Crossed pentachora of a cube with sides `above`: types mixed, and the types of case II.
+template <int... TY>
+__device__ __forceinline__ void pen_sets(std::integer_sequence<int, TY...>, unsigned above, unsigned& mixed,
+                                         unsigned& two) {
+  auto one = [&](int ty, int tets) {
+    mixed |= tets ? 1u << ty : 0u;
+    two |= tets == 3 ? 1u << ty : 0u;
+  };
+  (one(TY, pen_tets<TY>(above)), ...);
+}
+
+// Tetrahedra of every 64 listed cubes (one workgroup of iso_tess).
+__global__ __launch_bounds__(256) void iso_tess_count(const long long* __restrict__ list, long long n_list,
+                                                      int* __restrict__ cnt) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  unsigned n = 0;
+  if (i < n_list) n = (unsigned)pen_tets_all(std::make_integer_sequence<int, 24>{}, (unsigned)((u64)list[i] >> 48));
+  n = wave_sum(n);
+  if (lane_id() == 0 && i < n_list) cnt[i >> 6] = (int)n;
+}
+
+__global__ __launch_bounds__(64) void iso_tess(IsoGrid g, const long long* __restrict__ list,
+                                               const long long* __restrict__ tbase, long long n_list,
+                                               const unsigned* __restrict__ vinfo, const long long* __restrict__ hbase,
+                                               int* __restrict__ tets) {
+  __shared__ IsoTess W;
+  __shared__ IsoPenTables tab;
+  const int lane = threadIdx.x;
+  if (lane < 24) tab.chain[lane] = kIsoPenTables.chain[lane];
+  if (lane < 32) tab.split[lane] = kIsoPenTables.split[lane];
+  const long long i0 = (long long)blockIdx.x * 64;
+  const bool on = i0 + lane < n_list;
+  const u64 ent = (u64)list[min(i0 + lane, n_list - 1)];
+  const unsigned above = (unsigned)(ent >> 48);
+  const long long v = (long long)(ent & 0xFFFFFFFFFFFFull);
+  const long long row = v / g.nx;
+  const int x = (int)(v - row * g.nx);
+  // first hit and crossing mask of the cube's corners; a corner in a word without crossings anchors none, and what is
+  // read for it is not used
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const long long r = row + ((m & 1) + (((m >> 1) & 1) + (long long)((m >> 2) & 1) * g.nz) * g.ny);
+    const unsigned v0 = vinfo[r * g.nx + x], v1 = vinfo[r * g.nx + x + 1];
+    const long long b0 = hbase[r * g.nwx + (x >> 6)], b1 = hbase[r * g.nwx + ((x + 1) >> 6)];
+    W.corner[2 * m][lane] = make_uint2((unsigned)b0 + (v0 & 0xFFFFu), v0 >> 16);
+    W.corner[2 * m + 1][lane] = make_uint2((unsigned)b1 + (v1 & 0xFFFFu), v1 >> 16);
+  }
+  unsigned mixed = 0, two = 0;
+  pen_sets(std::make_integer_sequence<int, 24>{}, above, mixed, two);
+  if (!on) mixed = 0;
+  const unsigned incl = wave_incl_scan((unsigned)__popc(mixed));
+  const int n_pen = __builtin_amdgcn_readlane((int)incl, 63);
+  unsigned at = incl - (unsigned)__popc(mixed);
+  for (unsigned m = mixed; m; m &= m - 1u) W.pen[at++] = (unsigned short)((unsigned)lane | ((unsigned)__ffs((int)m) - 1u) << 6);
+  __syncthreads();
+  int4* T = reinterpret_cast<int4*>(tets) + tbase[blockIdx.x];
+  for (int p0 = 0; p0 < n_pen; p0 += 64) {
+    const int p = p0 + lane;
+    const unsigned pen = W.pen[min(p, n_pen - 1)];
+    const unsigned c = pen & 63u, chain = tab.chain[pen >> 6];
+    const unsigned side = (unsigned)__builtin_amdgcn_ds_bpermute((int)(c << 2), (int)above);
+    unsigned lm = 0;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) lm |= ((side >> ((chain >> (4 * k)) & 15u)) & 1u) << k;
+    const unsigned sp = tab.split[lm];
+    // hit index of the crossed edge between the chain positions in fields f and h
+    auto edge = [&](int f, int h) -> int {
+      const unsigned a = (sp >> (3 * f)) & 7u, b = (sp >> (3 * h)) & 7u;
+      const unsigned ca = (chain >> (4u * min(a, b))) & 15u, M = ((chain >> (4u * max(a, b))) & 15u) ^ ca;
+      const uint2 q = W.corner[ca][c];
+      return (int)q.x + __popc(q.y & ((1u << (M - 1u)) - 1u));
+    };
+    const bool prism = (sp >> 18) & 1u;
+    const unsigned mine = p < n_pen ? (prism ? 3u : 1u) : 0u, upto = wave_incl_scan(mine);
+    // case I: the lone vertex with the others in chain order; case II: (p1, a0..a2), (p2, a0..a2)
+    const int e0 = edge(0, 2), e1 = edge(0, 3), e2 = edge(0, 4);
+    int4* const o = W.out + (upto - mine);
+    if (mine == 1u) {
+      o[0] = make_int4(e0, e1, e2, edge(0, 5));
+    } else if (mine == 3u) {
+      const int e3 = edge(1, 2), e4 = edge(1, 3), e5 = edge(1, 4);
+      o[0] = make_int4(e0, e1, e2, e5);
+      o[1] = make_int4(e0, e1, e4, e5);
+      o[2] = make_int4(e0, e3, e4, e5);
+    }
+    __syncthreads();
+    const int n = __builtin_amdgcn_readlane((int)upto, 63);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (lane + 64 * q < n) T[lane + 64 * q] = W.out[lane + 64 * q];
+    T += n;
+    __syncthreads();  // the next 64 overwrite the staged ones
+  }
+}
+
+__global__ __launch_bounds__(256) void iso_label(const unsigned* __restrict__ hcomp, const long long* __restrict__ first,
+                                                 long long n, long long* __restrict__ label) {
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256)
+    label[i] = first[hcomp[i]];
+}
+
+unsigned blocks_of(long long n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
 hipError_t launch_iso_count(const float* f, int nx, int ny, int nz, int nt, float c, unsigned long long* bits,
-                            unsigned short* emask, unsigned char* hcnt, unsigned char* tcnt, unsigned* status,
+                            int* hcnt, int* acnt, int* rcnt, unsigned long long* n_tets, unsigned* status,
                             hipStream_t s) {
   const IsoGrid g{f, nx, ny, nz, nt, c, bits, (nx + 63) / 64};
   const long long n_words = (long long)nt * nz * ny * g.nwx;
   iso_bits<<<(unsigned)((n_words + 4 * kBitsWords - 1) / (4 * kBitsWords)), 256, 0, s>>>(g, n_words, bits, status);
-  iso_count<<<iso_grid(g), kIsoBX, 0, s>>>(g, emask, hcnt, tcnt, status);
+  iso_count<<<blocks_of(n_words) < 2048u ? blocks_of(n_words) : 2048u, 256, 0, s>>>(g, n_words, hcnt, acnt, rcnt, n_tets);
   return hipGetLastError();
 }
 
-hipError_t launch_iso_emit(const float* f, int nx, int ny, int nz, int nt, float c, const unsigned short* emask,
-                           const long long* hbase, const unsigned char* hcnt, long long* edge_id, float* pos,
-                           unsigned* parent, hipStream_t s) {
-  const IsoGrid g{f, nx, ny, nz, nt, c, nullptr, (nx + 63) / 64};
-  iso_emit<<<iso_grid(g), kIsoBX, 0, s>>>(g, emask, hbase, hcnt, edge_id, pos, parent);
+hipError_t launch_iso_components(int nx, int ny, int nz, int nt, const unsigned long long* bits,
+                                 const long long* rbase, long long n_runs, unsigned* parent, unsigned* comp,
+                                 long long* first, unsigned long long* n_comp, hipStream_t s) {
+  const IsoGrid g{nullptr, nx, ny, nz, nt, 0.0f, bits, (nx + 63) / 64};
+  const long long n_words = (long long)nt * nz * ny * g.nwx;
+  iso_runs_init<<<blocks_of(n_words), 256, 0, s>>>(g, n_words, rbase, parent);
+  const hipError_t e = launch_uf_compress(parent, n_runs, s);
+  if (e != hipSuccess) return e;
+  iso_runs_link<<<blocks_of(n_words), 256, 0, s>>>(g, n_words, rbase, parent);
+  iso_runs_done<<<blocks_of(n_runs), 256, 0, s>>>(parent, n_runs, comp, first, n_comp);
   return hipGetLastError();
 }
 
-hipError_t launch_iso_active(const unsigned char* tcnt, const long long* abase, long long V, long long* list,
-                             hipStream_t s) {
-  iso_active_list<<<(unsigned)((V + 255) / 256), 256, 0, s>>>(tcnt, abase, V, list);
-  return hipGetLastError();
-}
-
-hipError_t launch_iso_unite(const float* f, int nx, int ny, int nz, int nt, float c,
-                            const unsigned long long* bits, const long long* active, long long n_active,
-                            const unsigned short* emask, const long long* hbase, const unsigned char* hcnt,
-                            const unsigned char* tcnt, const long long* tbase, unsigned* parent, int* tets,
-                            unsigned* status, hipStream_t s) {
-  if (n_active == 0) return hipSuccess;
+hipError_t launch_iso_emit(const float* f, int nx, int ny, int nz, int nt, float c, const unsigned long long* bits,
+                           const int* hcnt, const long long* hbase, const long long* abase, const long long* rbase,
+                           const unsigned* comp, long long n_hits, long long n_active, unsigned* vinfo,
+                           long long* edge_id, float* pos, unsigned* hcomp, long long* first, long long* list,
+                           int* tcnt, long long* tbase, long long* scan_tmp, int* tets, long long* label,
+                           hipStream_t s) {
   const IsoGrid g{f, nx, ny, nz, nt, c, bits, (nx + 63) / 64};
-  iso_unite<<<(unsigned)((n_active + kIsoBX - 1) / kIsoBX), kIsoBX, 0, s>>>(g, active, n_active, emask, hbase, hcnt,
-                                                                            tcnt, tbase, parent, tets, status);
+  const long long n_words = (long long)nt * nz * ny * g.nwx;
+  iso_emit<<<(unsigned)((n_words + 4 * kIsoEmitWords - 1) / (4 * kIsoEmitWords)), 256, 0, s>>>(
+      g, n_words, hcnt, hbase, abase, rbase, comp, vinfo, edge_id, pos, hcomp, first, list);
+  if (n_active > 0) {
+    const long long groups = (n_active + 63) / 64;
+    iso_tess_count<<<blocks_of(n_active), 256, 0, s>>>(list, n_active, tcnt);
+    const hipError_t e = launch_scan(tcnt, tbase, groups, tbase + groups, scan_tmp, s);
+    if (e != hipSuccess) return e;
+    iso_tess<<<(unsigned)groups, 64, 0, s>>>(g, list, tbase, n_active, vinfo, hbase, tets);
+  }
+  const unsigned lb = blocks_of(n_hits);
+  iso_label<<<lb < 8192u ? lb : 8192u, 256, 0, s>>>(hcomp, first, n_hits, label);
   return hipGetLastError();
 }
 
