@@ -373,10 +373,12 @@ static void tune_store(int kind, long long nx, long long ny, int ty, int tt) {
 
 // Steps per slab for a kernel whose work units march `per_step` tiles through time: a slab of tt steps costs about
 // tt + extra plane passes, one after another, and the chip runs `resident` of them side by side before they slow each
-// other down.  The depth (at most `most`, slabs of even length) with the least (tt + extra) max(1, units / resident):
-// long slabs once the tiles of a step fill the chip, short ones when they would leave it idle (64 x 64 x 10 has eight
-// tiles a step).
+// other down.  The longest slab, `most`, when that leaves several rounds of units; else the depth (slabs of even length)
+// with the least (tt + extra) max(1, units / resident): short slabs when long ones would leave the chip idle (64 x 64 x
+// 10 has eight tiles a step: a call of 263 us with slabs of up to 16 steps in detection and emission, 115 us by this
+// rule).
 static int slab_steps(long long per_step, long long nt, int extra, long long resident, int most) {
+  if (per_step * ((nt + most - 1) / most) >= 4 * resident) return most < nt ? most : (int)nt;
   int best = 1;
   double best_cost = 1e300;
   for (int tt = 1; tt <= most && tt <= nt; ++tt) {
@@ -395,6 +397,12 @@ static int slab_steps(long long per_step, long long nt, int extra, long long res
 // Detection: wavefronts of 64 x 8 anchors; two of them per SIMD keep it issuing.  Workgroups of four wavefronts share
 // halo rows in the CU's cache; when there is less than a wavefront per SIMD, single ones spread over more CUs.
 constexpr long long kDetResident = 2048;
+
+// Tiled emission: workgroups of 64 x 8 anchors, four to a CU; a slab also loads the slices before and after it.
+constexpr long long kEmitResident = 1024;
+static int emit_steps(const Grid2& g) {
+  return slab_steps((long long)g.nxt * ((g.ny + kEmitRows - 1) / kEmitRows), g.t_end - g.t_begin, 2, kEmitResident, kEmitSteps);
+}
 
 static void tuned_tiles2(const ftk_options& o, int kind, long long nx, long long ny, int nt, int* ty, int* tt) {
   const long long waves = ((nx + 63) / 64) * ((ny + kDetectRows - 1) / kDetectRows);
@@ -581,7 +589,7 @@ ftk_status track2d_core(const float* field, ftk_field_kind kind, int64_t nx, int
       if (he == hipSuccess)
         he = launch_emit2d_sparse(g, wide, masks, seg_cnt, seg_off, od, &dctl->status, dctl->cnt, s);
     } else {
-      he = launch_emit2d(g, wide, masks, seg_cnt, seg_off, od, &dctl->status, dctl->cnt, s);
+      he = launch_emit2d(g, wide, emit_steps(g), masks, seg_cnt, seg_off, od, &dctl->status, dctl->cnt, s);
     }
     ph.mark(4);
     if (he == hipSuccess && sparse) he = launch_uf_compress(parent, nh, s);
@@ -829,7 +837,7 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
                                 ftk_cp_result* outs) {
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
-  constexpr int TYD = kDetectRows, TYE = 8;  // rows of a detection wavefront, of an emission tile
+  constexpr int TYD = kDetectRows, TYE = kEmitRows;  // rows of a detection wavefront, of an emission tile
   // slab depth: the option, else the tuned one of the series with the most vertices, else the rule for all tiles
   int ttd = o.slab_depth;
   if (!ttd) {

@@ -23,7 +23,6 @@ namespace ftk {
 namespace {
 
 constexpr int TX = 64;
-constexpr int kEmitTT = 16;  // steps per emission workgroup
 
 constexpr float kNarrow2 = 16777216.0f;  // 2^24: cofactors and their sum stay exact in binary64 below it
 
@@ -799,7 +798,7 @@ __device__ __forceinline__ void emit2d_tile(const Grid2& g, int TT, int bx, int 
   constexpr int FW = TX + 5, FH = TY + 5;  // scalar field: x0-2 .. x0+TX+2
   constexpr int RW = TX + 2, RH = TY + 2;  // mask slices: x0-1 .. x0+TX, y0-1 .. y0+TY
   constexpr int CAP = 2048;                // local union-find capacity (hits)
-  constexpr int MAXTT = kEmitTT;           // step tables (TT <= kEmitTT)
+  constexpr int MAXTT = kEmitSteps;        // step tables (TT <= kEmitSteps)
   __shared__ float2 gs[2][GH * GW];
   // Mask slices of steps t-1, t, t+1 (ring slot = step mod 3) over the tile's anchors with a one-anchor halo: hit
   // masks, first hit of each anchor relative to its row segment's first hit (left halo column: minus its hit
@@ -1797,9 +1796,9 @@ hipError_t launch_emit2d_batched(const Series2* S, const int* prefix, int nser, 
   int blocks = total_items < 1536 ? total_items : 1536;
   if (blocks < 1) blocks = 1;
   if (wide)
-    emit2d_batched<8, true><<<blocks, 256, 0, s>>>(S, prefix, nser, kEmitTT, counter, status, work_cnt);
+    emit2d_batched<8, true><<<blocks, 256, 0, s>>>(S, prefix, nser, kEmitSteps, counter, status, work_cnt);
   else
-    emit2d_batched<8, false><<<blocks, 256, 0, s>>>(S, prefix, nser, kEmitTT, counter, status, work_cnt);
+    emit2d_batched<8, false><<<blocks, 256, 0, s>>>(S, prefix, nser, kEmitSteps, counter, status, work_cnt);
   return hipGetLastError();
 }
 
@@ -1817,16 +1816,16 @@ hipError_t launch_detect2d(const Grid2& g, int ty, int tt, uint16_t* masks, int*
   return hipGetLastError();
 }
 
-hipError_t launch_emit2d(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
+hipError_t launch_emit2d(const Grid2& g, bool wide, int tt, const uint16_t* masks, const int* seg_cnt,
                          const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
                          hipStream_t s) {
-  constexpr int TYE = 8, TTE = kEmitTT;
-  static_assert(TTE <= 32, "steps per emission tile exceed the tile's step tables");
-  dim3 grid((unsigned)g.nxt, (unsigned)((g.ny + TYE - 1) / TYE), (unsigned)((g.t_end - g.t_begin + TTE - 1) / TTE));
+  static_assert(kEmitSteps <= 32, "steps per emission tile exceed the tile's step tables");
+  dim3 grid((unsigned)g.nxt, (unsigned)((g.ny + kEmitRows - 1) / kEmitRows),
+            (unsigned)((g.t_end - g.t_begin + tt - 1) / tt));
   if (wide)
-    emit2d<TYE, true><<<grid, 256, 0, s>>>(g, TTE, masks, seg_cnt, seg_off, o, status, cnt);
+    emit2d<kEmitRows, true><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, seg_off, o, status, cnt);
   else
-    emit2d<TYE, false><<<grid, 256, 0, s>>>(g, TTE, masks, seg_cnt, seg_off, o, status, cnt);
+    emit2d<kEmitRows, false><<<grid, 256, 0, s>>>(g, tt, masks, seg_cnt, seg_off, o, status, cnt);
   return hipGetLastError();
 }
 

@@ -79,7 +79,9 @@ constexpr int kDetectRows = 8;  // anchor rows of a detection wavefront
 // 2^24 (the emission then takes its 128-bit form) and ST_RANGE when one reaches 2^62.
 hipError_t launch_detect2d(const Grid2& g, int ty, int tt, uint16_t* masks, int* seg_cnt, unsigned* status,
                            hipStream_t s);
-hipError_t launch_emit2d(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
+// Tiled emission: workgroups of 64 x kEmitRows anchors marching through slabs of tt (at most kEmitSteps) steps.
+constexpr int kEmitRows = 8, kEmitSteps = 16;
+hipError_t launch_emit2d(const Grid2& g, bool wide, int tt, const uint16_t* masks, const int* seg_cnt,
                          const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
                          hipStream_t s);
 
