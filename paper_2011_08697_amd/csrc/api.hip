@@ -720,37 +720,36 @@ ftk_status track3d_impl(const float* field, int64_t nx, int64_t ny, int64_t nz, 
   long long* seg_off = sc.get<long long>((size_t)nseg);
   long long* scan_tmp = sc.get<long long>(scan_tmp_elems(nseg));
   Ctl* dctl = sc.get<Ctl>(1);
-  g.cert = sc.get<unsigned char>((size_t)(nt * cert3_plane(g)));
-  if (!masks || !seg_cnt || !seg_off || !scan_tmp || !dctl || !g.cert)
+  const long long tile_steps = nt * cert3_plane(g);
+  g.cert = sc.get<unsigned char>((size_t)tile_steps);
+  unsigned long long* facts = sc.get<unsigned long long>((size_t)tile_steps);
+  uint2* runs = sc.get<uint2>((size_t)tile_steps);
+  if (!masks || !seg_cnt || !seg_off || !scan_tmp || !dctl || !g.cert || !facts || !runs)
     return fail(FTK_ERR_OOM, "scratch allocation failed");
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
-  int tt = o.slab_depth ? o.slab_depth : 8;
-  if (tt > g.nt) tt = g.nt;
+  // Steps of a tile that one workgroup takes: a run costs one plane more than it has steps, so long runs once there
+  // are many per workgroup in flight.
+  const int tt = o.slab_depth ? std::min(o.slab_depth, 16) : (int)std::min(8ll, std::max(1ll, tile_steps / 16384));
   Ctl h;
   bool wide = false;
   Phases ph;
   ph.init(o.profile != 0, s);
   ph.mark(0);
-  HIP_TRY(launch_detect3d(g, tt, false, masks, seg_cnt, &dctl->status, s));
-  ph.mark(1);
-  HIP_TRY(launch_scan(seg_cnt, seg_off, nseg, &dctl->total, scan_tmp, s));
-  ph.mark(2);
-  ftk_status st = read_ctl(&h, dctl, s);
-  if (st) return st;
-  if (h.status & ST_NONFINITE) return decode_status(h.status);
-  if (h.status & ST_WIDE) {
-    wide = true;
-    HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
-    ph.mark(0);
-    HIP_TRY(launch_detect3d(g, tt, true, masks, seg_cnt, &dctl->status, s));
+  HIP_TRY(launch_fill_words((unsigned*)seg_cnt, 0u, nseg, s));
+  HIP_TRY(launch_facts3d(g, tt, facts, runs, &dctl->cnt[CNT_RUNS], &dctl->status, s));
+  ftk_status st;
+  for (;;) {
+    HIP_TRY(launch_detect3d(g, wide, runs, &dctl->cnt[CNT_RUNS], &dctl->cnt[CNT_TAKEN], masks, seg_cnt, &dctl->status, s));
     ph.mark(1);
     HIP_TRY(launch_scan(seg_cnt, seg_off, nseg, &dctl->total, scan_tmp, s));
     ph.mark(2);
     st = read_ctl(&h, dctl, s);
+    if (!st) st = decode_status(h.status);
     if (st) return st;
+    if (wide || !(h.status & ST_WIDE)) break;
+    wide = true;
+    HIP_TRY(launch_fill_words((unsigned*)&dctl->cnt[CNT_TAKEN], 0u, 2, s));
   }
-  st = decode_status(h.status);
-  if (st) return st;
   const long long nh = h.total;
   if (nh > 0xFFFFFFFELL) {
     out->n_hits = nh;
@@ -769,8 +768,7 @@ ftk_status track3d_impl(const float* field, int64_t nx, int64_t ny, int64_t nz, 
   if (outs & FTK_OUT_LABEL) r.label = (int64_t*)al.get(sizeof(int64_t) * nh);
   unsigned* parent = sc.get<unsigned>((size_t)nh);
   uint2* work = sc.get<uint2>((size_t)nh);
-  long long* list = sc.get<long long>((size_t)nh);  // row chunks with hits: at most one per hit
-  bool oom = !r.face_id || !parent || !work || !list || ((outs & FTK_OUT_POS) && !r.pos) || ((outs & FTK_OUT_MU) && !r.mu) ||
+  bool oom = !r.face_id || !parent || !work || ((outs & FTK_OUT_POS) && !r.pos) || ((outs & FTK_OUT_MU) && !r.mu) ||
              ((outs & FTK_OUT_TYPE) && !r.type) || ((outs & FTK_OUT_FLAGS) && !r.flags) ||
              ((outs & FTK_OUT_LABEL) && !r.label);
   if (oom) {
@@ -788,8 +786,7 @@ ftk_status track3d_impl(const float* field, int64_t nx, int64_t ny, int64_t nz, 
   hipError_t he = hipSuccess;
   ph.mark(3);
   if (nh > 0) {
-    he = launch_emit3d(g, wide, masks, seg_cnt, seg_off, nh, od, &dctl->status, dctl->cnt, list, &dctl->cnt[CNT_LIST],
-                       s);
+    he = launch_emit3d(g, wide, masks, seg_cnt, seg_off, 0, nh, od, &dctl->status, dctl->cnt, s);
     ph.mark(4);
     if (he == hipSuccess) he = launch_uf_hook(parent, work, &dctl->cnt[CNT_WORK], nh, s);
     if (he == hipSuccess) he = launch_uf_label(parent, od.face_id, (long long*)r.label, nh, dctl->cnt, s);
@@ -1074,8 +1071,9 @@ struct ftk_tracker {
   float* fring = nullptr;
   uint16_t* mring = nullptr;
   uint64_t* mring3 = nullptr;
-  long long* list3 = nullptr;  // 3D emission: 64-vertex row chunks with hits of the emitted step
   unsigned char* cert3 = nullptr;  // 3D: certified detection tile-steps (ring of 3 planes)
+  unsigned long long* facts3 = nullptr;  // 3D: sign facts of the tiles (ring of 3 planes)
+  uint2* runs3 = nullptr;                // 3D: tiles to be tested at the detected step
   int* cring = nullptr;
   long long* oring = nullptr;
   long long* scan_tmp = nullptr;
@@ -1103,14 +1101,15 @@ static Alloc tracker_alloc(ftk_tracker* h) { return make_alloc(h->o, h->s); }
 static void tracker_free_all(ftk_tracker* h) {
   const Alloc al = tracker_alloc(h);
   (void)hipStreamSynchronize(h->s);
-  void* ps[] = {h->fring, h->mring, h->mring3, h->list3, h->cert3, h->cring, h->oring, h->scan_tmp, h->dctl,
+  void* ps[] = {h->fring, h->mring, h->mring3, h->cert3, h->facts3, h->runs3, h->cring, h->oring, h->scan_tmp, h->dctl,
                 h->dplane, h->face_id, h->pos, h->mu, h->type, h->flags, h->parent, h->work};
   for (void* p : ps) al.put(p);
   h->fring = nullptr;
   h->mring = nullptr;
   h->mring3 = nullptr;
-  h->list3 = nullptr;
   h->cert3 = nullptr;
+  h->facts3 = nullptr;
+  h->runs3 = nullptr;
   h->cring = nullptr;
   h->oring = nullptr;
   h->scan_tmp = nullptr;
@@ -1255,19 +1254,22 @@ static ftk_status tracker_detect3(ftk_tracker* h, int p, int nt) {
   const int slot = p % 3;
   int* cnt = h->cring + (size_t)slot * h->nseg_plane;
   long long* off = h->oring + (size_t)slot * h->nseg_plane;
-  for (int pass = 0; pass < 2; ++pass) {
-    const bool wide = pass == 1;
-    zero_words<<<1, 64, 0, h->s>>>(&dctl->dstatus, 1);
+  zero_words<<<1, 64, 0, h->s>>>(&dctl->dstatus, 1);
+  zero_words<<<1, 64, 0, h->s>>>((unsigned*)&dctl->cnt[CNT_RUNS], 4);  // and CNT_TAKEN
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(launch_fill_words((unsigned*)cnt, 0u, h->nseg_plane, h->s));
+  HIP_TRY(launch_facts3d(g, 1, h->facts3, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->dstatus, h->s));
+  unsigned st = 0;
+  HIP_TRY(launch_detect3d(g, false, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->cnt[CNT_TAKEN], h->mring3, h->cring, &dctl->dstatus, h->s));
+  HIP_TRY(hipMemcpyAsync(&st, &dctl->dstatus, sizeof(unsigned), hipMemcpyDeviceToHost, h->s));
+  HIP_TRY(hipStreamSynchronize(h->s));
+  if (st & (ST_NONFINITE | ST_RANGE)) return decode_status(st);
+  h->plane_wide[slot] = (st & ST_WIDE) ? 1 : 0;
+  if (st & ST_WIDE) {
+    zero_words<<<1, 64, 0, h->s>>>((unsigned*)&dctl->cnt[CNT_TAKEN], 2);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(launch_detect3d(g, 1, wide, h->mring3, h->cring, &dctl->dstatus, h->s));
-    unsigned st = 0;
-    HIP_TRY(hipMemcpyAsync(&st, &dctl->dstatus, sizeof(unsigned), hipMemcpyDeviceToHost, h->s));
-    HIP_TRY(hipStreamSynchronize(h->s));
-    if (st & (ST_NONFINITE | ST_RANGE)) return decode_status(st);
-    if (!(st & ST_WIDE)) {
-      h->plane_wide[slot] = wide ? 1 : 0;
-      break;
-    }
+    HIP_TRY(launch_detect3d(g, true, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->cnt[CNT_TAKEN], h->mring3, h->cring,
+                            &dctl->dstatus, h->s));
   }
   HIP_TRY(launch_scan(cnt, off, h->nseg_plane, h->dplane, h->scan_tmp, h->s));
   add_plane_base<<<(unsigned)((h->nseg_plane + 255) / 256), 256, 0, h->s>>>(off, h->nseg_plane, &dctl->total);
@@ -1293,11 +1295,8 @@ static ftk_status tracker_emit3(ftk_tracker* h, int e, int nt) {
   od.parent = h->parent;
   od.work = h->work;
   const long long step_hits = h->total_after[e] - (e > 0 ? h->total_after[e - 1] : 0);
-  zero_words<<<1, 64, 0, h->s>>>((unsigned*)&dctl->cnt[CNT_LIST], 2);
-  HIP_TRY(hipGetLastError());
-  if (step_hits > 0)
-    HIP_TRY(launch_emit3d(g, h->plane_wide[e % 3] != 0, h->mring3, h->cring, h->oring, step_hits, od, &dctl->status,
-                          dctl->cnt, h->list3, &dctl->cnt[CNT_LIST], h->s));
+  HIP_TRY(launch_emit3d(g, h->plane_wide[e % 3] != 0, h->mring3, h->cring, h->oring, h->total_after[e] - step_hits,
+                        step_hits, od, &dctl->status, dctl->cnt, h->s));
   h->emitted = h->total_after[e];
   return FTK_OK;
 }
@@ -1336,12 +1335,13 @@ extern "C" ftk_status ftk_cp_create(int32_t n, const int64_t* dims, ftk_field_ki
       h->mring = (uint16_t*)al.get(sizeof(uint16_t) * 3 * plane);
     } else {
       h->mring3 = (uint64_t*)al.get(sizeof(uint64_t) * 3 * plane);
-      h->list3 = (long long*)al.get(sizeof(long long) * h->nz * h->ny * ((h->nx + 63) / 64));
       ftk::Grid3 gd;
       gd.nx = (int)h->nx;
       gd.ny = (int)h->ny;
       gd.nz = (int)h->nz;
       h->cert3 = (unsigned char*)al.get((size_t)(3 * ftk::cert3_plane(gd)));
+      h->facts3 = (unsigned long long*)al.get(sizeof(unsigned long long) * 3 * (size_t)ftk::cert3_plane(gd));
+      h->runs3 = (uint2*)al.get(sizeof(uint2) * (size_t)ftk::cert3_plane(gd));
     }
     h->cring = (int*)al.get(sizeof(int) * 3 * h->nseg_plane);
     h->oring = (long long*)al.get(sizeof(long long) * 3 * h->nseg_plane);
@@ -1349,7 +1349,7 @@ extern "C" ftk_status ftk_cp_create(int32_t n, const int64_t* dims, ftk_field_ki
     h->dctl = al.get(sizeof(Ctl));
     h->dplane = (long long*)al.get(sizeof(long long));
     const bool ring_ok =
-        n == 2 ? h->mring != nullptr : (h->mring3 != nullptr && h->list3 != nullptr && h->cert3 != nullptr);
+        n == 2 ? h->mring != nullptr : (h->mring3 && h->cert3 && h->facts3 && h->runs3);
     if (!h->fring || !ring_ok || !h->cring || !h->oring || !h->scan_tmp || !h->dctl || !h->dplane) {
       ftk::tracker_free_all(h);
       delete h;

@@ -105,11 +105,21 @@ hipError_t launch_emit2d_batched(const Series2* S, const int* prefix, int nser, 
 hipError_t launch_uf_label_batched(unsigned* parent, const Series2* S, const unsigned* gbase, int nser, long long n,
                                    hipStream_t s);
 
-hipError_t launch_detect3d(const Grid3& g, int tt, bool wide, uint64_t* masks, int* seg_cnt, unsigned* status,
+// 3D detection of the steps [t_begin, t_end).  launch_facts3d marks the tile-steps proved empty (g.cert), lists the runs
+// of the others (at most `most` <= 16 steps each; runs: cert3_plane entries per step, *n_runs counts up from its value)
+// and reports non-finite and out-of-range values; launch_detect3d tests the listed runs and writes their masks and counts
+// (the counts of the other tile-steps are the caller's to clear).  facts: cert3_plane words per plane, stored like the
+// masks (ring slots included), planes t_begin .. t_end.  The narrow variant does nothing once ST_WIDE is set.
+hipError_t launch_facts3d(const Grid3& g, int most, unsigned long long* facts, uint2* runs, unsigned long long* n_runs,
+                          unsigned* status, hipStream_t s);
+// taken: work counter, zero before the call.
+hipError_t launch_detect3d(const Grid3& g, bool wide, const uint2* runs, const unsigned long long* n_runs,
+                           unsigned long long* taken, uint64_t* masks, int* seg_cnt, const unsigned* status,
                            hipStream_t s);
+// Emission of the n_hits hits of the steps [t_begin, t_end), whose output indices start at `first`.
 hipError_t launch_emit3d(const Grid3& g, bool wide, const uint64_t* masks, const int* seg_cnt,
-                         const long long* seg_off, long long n_hits, const Out3& o, unsigned* status,
-                         unsigned long long* cnt, long long* list, unsigned long long* list_n, hipStream_t s);
+                         const long long* seg_off, long long first, long long n_hits, const Out3& o, unsigned* status,
+                         unsigned long long* cnt, hipStream_t s);
 
 // Exclusive scan of n int32 counts into int64 offsets; total written to *total (device).  tmp must hold
 // scan_tmp_elems(n) int64 values.
