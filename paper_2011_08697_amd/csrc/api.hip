@@ -2045,17 +2045,21 @@ ftk_status ftk_track_vortex3d(const float* psi, int64_t nx, int64_t ny, int64_t 
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
   const long long V = nx * ny * nz * nt;
+  const long long NW = ((nx + 63) / 64) * ny * nz * nt;  // words of 64 vertices of a row
   unsigned short* emask = sc.get<unsigned short>((size_t)V);
   unsigned long long* tmask = sc.get<unsigned long long>((size_t)V);
-  unsigned char* cnt = sc.get<unsigned char>((size_t)V);
-  long long* hoff = sc.get<long long>((size_t)V);
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(V));
+  unsigned short* before = sc.get<unsigned short>((size_t)V);
+  int* wcnt = sc.get<int>((size_t)NW);
+  long long* wbase = sc.get<long long>((size_t)NW);
+  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(NW));
   Ctl* dctl = sc.get<Ctl>(1);
-  if (!emask || !tmask || !cnt || !hoff || !tmp || !dctl) return fail(FTK_ERR_OOM, "scratch allocation failed");
+  if (!emask || !tmask || !before || !wcnt || !wbase || !tmp || !dctl)
+    return fail(FTK_ERR_OOM, "scratch allocation failed");
   const float qscale = std::ldexp(1.0f, o.quant_log2);
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
-  HIP_TRY(ftk::launch_vx_detect(psi, (int)nx, (int)ny, (int)nz, (int)nt, qscale, emask, tmask, cnt, &dctl->status, s));
-  HIP_TRY(ftk::launch_scan_u8(cnt, hoff, V, &dctl->total, tmp, s));
+  HIP_TRY(ftk::launch_vx_detect(psi, (int)nx, (int)ny, (int)nz, (int)nt, qscale, emask, tmask, before, wcnt,
+                                &dctl->status, s));
+  HIP_TRY(ftk::launch_scan(wcnt, wbase, NW, &dctl->total, tmp, s));
   Ctl h;
   st = read_ctl(&h, dctl, s);
   if (st) return st;
@@ -2076,8 +2080,8 @@ ftk_status ftk_track_vortex3d(const float* psi, int64_t nx, int64_t ny, int64_t 
   }
   hipError_t he = hipSuccess;
   if (nh > 0) {
-    he = ftk::launch_vx_emit(psi, (int)nx, (int)ny, (int)nz, (int)nt, qscale, tmask, hoff, (long long*)r.tri_id, r.pos,
-                             parent, s);
+    he = ftk::launch_vx_emit(psi, (int)nx, (int)ny, (int)nz, (int)nt, qscale, tmask, before, wcnt, wbase, nh,
+                             (long long*)r.tri_id, r.pos, parent, s);
     if (he == hipSuccess)
       he = ftk::launch_uf_label(parent, (const long long*)r.tri_id, (long long*)r.label, nh, dctl->cnt, s);
   }

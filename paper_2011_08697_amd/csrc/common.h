@@ -74,6 +74,49 @@ __device__ __forceinline__ float diff3(float lo, float mid, float hi, int i, int
 __device__ __forceinline__ float quant(float v, float scale) { return rintf(v * scale); }
 
 // ---------------------------------------------------------------------------------------------------------------
+// Lanes of a wavefront as consecutive vertices of a row.
+// ---------------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// v of the next lane; lane 63 takes `past`
+__device__ __forceinline__ unsigned from_next(unsigned v, unsigned past) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)past, (int)v, 0x130, 0xf, 0xf, false);  // wave_shl:1
+}
+__device__ __forceinline__ float from_next(float v, float past) {
+  return __int_as_float((int)from_next((unsigned)__float_as_int(v), (unsigned)__float_as_int(past)));
+}
+// v of the previous lane; lane 0 takes `before`
+__device__ __forceinline__ float from_prev(float v, float before) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(__float_as_int(before), __float_as_int(v), 0x138, 0xf, 0xf, false));  // wave_shr:1
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Simulation of Simplicity for the 2x2 determinant of the columns a (lower vertex index) and b.  Each entry (j, k)
+// carries eps^(2^(2k+j)); the perturbed determinant is
+//   (a0 b1 - a1 b0) + b1 e^1 - b0 e^2 - a1 e^4 - e^6 + a0 e^8 + e^9,
+// so its sign is that of the first nonzero of (det, b1, -b0, -a1, -1).
+//
+// The entries are quantised components, roundings of binary32 values: at most 24 significant bits at any magnitude, so
+// the product a1 b0 is exact in binary64 and the fused operation rounds the exact determinant once -- its sign, zero
+// included, is the exact one.  edge_tie gives the perturbation's sign for an exact zero as a full mask, ~0 for negative
+// (on the high words, without branches; a shifted-out sign leaves 0 for +-0).
+// ---------------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ double edge_det(double a0, double a1, double b0, double b1) {
+  return __builtin_fma(a0, b1, -(a1 * b0));
+}
+__device__ __forceinline__ int edge_tie(double a1, double b0, double b1) {
+  const int ha1 = __double2hiint(a1), hb0 = __double2hiint(b0), hb1 = __double2hiint(b1);
+  int s = (ha1 << 1) != 0 ? ~ha1 : -1;
+  s = (hb0 << 1) != 0 ? ~hb0 : s;
+  s = (hb1 << 1) != 0 ? hb1 : s;
+  return s >> 31;
+}
+// ~0 for a negative determinant, else 0 (either for a zero, which the caller settles with edge_tie)
+__device__ __forceinline__ int edge_neg(double d) { return __double2hiint(d) >> 31; }
+
+// ---------------------------------------------------------------------------------------------------------------
 // Classification (Sec. 4.1): types from the spatial Jacobian interpolated at the zero, J_c = sum mu_i J(v_i).
 // Reference semantics are binary64 in a fixed order; the FP32 evaluation is accepted only when every sign it
 // decides is certified: |value32| > E32 + E64, where E32 and E64 bound the distance of the binary32 and binary64

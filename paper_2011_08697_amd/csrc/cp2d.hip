@@ -73,19 +73,6 @@ constexpr int kDetRaw = kDetRows + 3;      // scalar field rows behind them
 
 typedef unsigned long long u64;
 
-__device__ __forceinline__ float lane_value(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-// v of the next lane; lane 63 takes `past`
-__device__ __forceinline__ float from_next(float v, float past) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(past), __float_as_int(v), 0x130, 0xf, 0xf, false));  // wave_shl:1
-}
-// v of the previous lane; lane 0 takes `before`
-__device__ __forceinline__ float from_prev(float v, float before) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(before), __float_as_int(v), 0x138, 0xf, 0xf, false));  // wave_shr:1
-}
 // v of lane i - 1 / i + 1 within the first 16 lanes (lanes without a source keep their own)
 __device__ __forceinline__ float row_prev(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x111, 0xf, 0xf, false));
@@ -107,23 +94,6 @@ struct DetPlane {
   float h[2];
 };
 
-// Simulation of Simplicity for the 2x2 determinant of the columns a (lower vertex index) and b.  Each entry (j, k)
-// carries eps^(2^(2k+j)); the perturbed determinant is
-//   (a0 b1 - a1 b0) + b1 e^1 - b0 e^2 - a1 e^4 - e^6 + a0 e^8 + e^9,
-// so its sign is that of the first nonzero of (det, b1, -b0, -a1, -1): edge_tie gives it for an exact zero,
-__device__ __forceinline__ double edge_det(double a0, double a1, double b0, double b1) {
-  return __builtin_fma(a0, b1, -(a1 * b0));
-}
-// as a full mask, ~0 for negative (on the high words, without branches; a shifted-out sign leaves 0 for +-0).
-__device__ __forceinline__ int edge_tie(double a1, double b0, double b1) {
-  const int ha1 = __double2hiint(a1), hb0 = __double2hiint(b0), hb1 = __double2hiint(b1);
-  int s = (ha1 << 1) != 0 ? ~ha1 : -1;
-  s = (hb0 << 1) != 0 ? ~hb0 : s;
-  s = (hb1 << 1) != 0 ? hb1 : s;
-  return s >> 31;
-}
-// ~0 for a negative determinant, else 0 (either for a zero, which the caller settles with edge_tie)
-__device__ __forceinline__ int edge_neg(double d) { return __double2hiint(d) >> 31; }
 // Smallest of z and the magnitudes of the high words of two determinants, read as binary32: zero iff one of the
 // determinants is zero (a nonzero one is an integer, whose high word is that of a value of at least one).
 __device__ __forceinline__ float zero_seen(float z, double d, double e) {
@@ -163,9 +133,6 @@ static_assert((kGOwn & kGXy) == 0 && kSpread.gxy[4] != 0, "distinct E0 bits in t
 constexpr unsigned types_using(int axis) { return (unsigned)types_using_axis(kTri2, axis); }
 
 __device__ __forceinline__ unsigned spread(int neg, unsigned bits, unsigned acc) { return ((unsigned)neg & bits) | acc; }
-__device__ __forceinline__ unsigned from_next(unsigned v, unsigned past) {
-  return (unsigned)__builtin_amdgcn_update_dpp((int)past, (int)v, 0x130, 0xf, 0xf, false);  // wave_shl:1
-}
 
 }  // namespace
 

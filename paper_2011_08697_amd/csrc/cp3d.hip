@@ -207,18 +207,6 @@ constexpr int ord_bit(int ti) {
 // ---------------------------------------------------------------------------------------------------------------
 namespace {
 
-__device__ __forceinline__ float f3_lane(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ float f3_next(float v, float past) {  // lane l: v of lane l + 1; lane 63: past
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(past), __float_as_int(v), 0x130, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float f3_prev(float v, float before) {  // lane l: v of lane l - 1; lane 0: before
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(before), __float_as_int(v), 0x138, 0xf, 0xf, false));
-}
-
 // Extrema of the three components over a set of vertices, and the facts they give.
 struct Extrema3 {
   float mn[3], mx[3];
@@ -297,7 +285,7 @@ __global__ __launch_bounds__(256) void facts3d(Grid3 g, int t_first, unsigned lo
         if (y < ny) {  // uniform
           const float f = cur[ly + 1];
           nonfinite = __builtin_fmaf(f, 0.0f, nonfinite);
-          const float lo = f3_prev(f, f3_lane(side, lz * 8 + ly)), hi = f3_next(f, f3_lane(side, 32 + lz * 8 + ly));
+          const float lo = from_prev(f, lane_value(side, lz * 8 + ly)), hi = from_next(f, lane_value(side, 32 + lz * 8 + ly));
           const float sy = __int_as_float((y == 0 || y == ny - 1) ? one_bits : half_bits);
           const float q[3] = {rintf((hi - lo) * sx), rintf((cur[ly + 2] - cur[ly]) * sy),
                               rintf((next[ly + 1] - prev[ly]) * sz)};

@@ -125,9 +125,6 @@ hipError_t launch_emit3d(const Grid3& g, bool wide, const uint64_t* masks, const
 // scan_tmp_elems(n) int64 values.
 size_t scan_tmp_elems(long long n);
 hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s);
-// the same over byte counts (per-vertex or per-face counts below 256)
-hipError_t launch_scan_u8(const unsigned char* in, long long* out, long long n, long long* total, long long* tmp,
-                          hipStream_t s);
 
 // Trajectory post-processing (post.hip).
 hipError_t launch_traj_table(int n, const int64_t* dims_with_t, const long long* face_id, const long long* label,
@@ -190,13 +187,17 @@ hipError_t launch_iso_emit(const float* f, int nx, int ny, int nz, int nt, float
                            int* tcnt, long long* tbase, long long* scan_tmp, int* tets, long long* label,
                            hipStream_t s);
 
-// Quantum vortex surfaces (vortex.hip): edge signs and positive-triangle masks (tmask, 50 bits) with per-vertex
-// counts; then emission of triangle ids, points and identity parents, and the pentachoron unions.  Grids of (ceil(nx / 128), ny, nz * nt) blocks (ny, nz * nt <= 65535).
+// Quantum vortex surfaces (vortex.hip): edge signs, positive-triangle masks (tmask, 50 bits), the triangles before each
+// vertex in its word of 64 vertices of a row, and the words' counts (ceil(nx / 64) * ny * nz * nt); then, with their
+// scan wbase, triangle ids, points and the union-find forest.  Grids of (ceil(nx / 128), ny, nz * nt) blocks
+// (ny, nz * nt <= 65535).
 hipError_t launch_vx_detect(const float* psi, int nx, int ny, int nz, int nt, float qscale, unsigned short* emask,
-                            unsigned long long* tmask, unsigned char* cnt, unsigned* status, hipStream_t s);
+                            unsigned long long* tmask, unsigned short* before, int* wcnt, unsigned* status,
+                            hipStream_t s);
 hipError_t launch_vx_emit(const float* psi, int nx, int ny, int nz, int nt, float qscale,
-                          const unsigned long long* tmask, const long long* hoff, long long* tri_id, float* pos,
-                          unsigned* parent, hipStream_t s);
+                          const unsigned long long* tmask, const unsigned short* before, const int* wcnt,
+                          const long long* wbase, long long n_hits, long long* tri_id, float* pos, unsigned* parent,
+                          hipStream_t s);
 // Critical points on an extruded triangle mesh (prism.hip): face tests over nt * S faces (flag, allocated to a
 // multiple of 16 bytes), then emission and the tetrahedron unions, with the hit offsets from the group bases of the
 // flags (offsets16.h).

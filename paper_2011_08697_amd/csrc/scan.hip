@@ -1,4 +1,4 @@
-// scan.hip -- exclusive prefix sum of per-segment hit counts (int32 or byte counts -> int64 offsets), the compaction
+// scan.hip -- exclusive prefix sum of per-segment hit counts (int32 counts -> int64 offsets), the compaction
 // step that gives every punctured simplex its position in the face-id-sorted output.
 #include "common.h"
 #include "internal.h"
@@ -97,11 +97,6 @@ hipError_t scan_any(const T* in, long long* out, long long n, long long* total, 
 
 hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s) {
   return scan_any<int>(in, out, n, total, tmp, s);
-}
-
-hipError_t launch_scan_u8(const unsigned char* in, long long* out, long long n, long long* total, long long* tmp,
-                          hipStream_t s) {
-  return scan_any<unsigned char>(in, out, n, total, tmp, s);
 }
 
 }  // namespace ftk
