@@ -1603,21 +1603,24 @@ ftk_status ftk_traj_table_build(const ftk_cp_result* r, int32_t n, const int64_t
   t.t_min = (float*)al.get(sizeof(float) * ntr);
   t.t_max = (float*)al.get(sizeof(float) * ntr);
   t.n_ends = (int32_t*)al.get(sizeof(int32_t) * ntr);
-  int* flag = sc.get<int>((size_t)nh);
-  long long* off = sc.get<long long>((size_t)nh);
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(nh));
-  long long* rb = sc.get<long long>((size_t)ftk::row_buckets(n, dims_with_t) + 1);
+  const size_t nw = (size_t)((nh + 63) / 64);
+  ftk::TableScratch ts;
+  ts.bits = sc.get<unsigned long long>(nw);
+  ts.cnt = sc.get<int>(nw);
+  ts.base = sc.get<long long>(nw);
+  ts.scan_tmp = sc.get<long long>(ftk::scan_tmp_elems((long long)nw));
+  ts.table = sc.get<char>(ftk::traj_table_bytes(n, dims_with_t, nh));
   Ctl* dctl = sc.get<Ctl>(1);
-  if (!t.label || !t.n_points || !t.t_min || !t.t_max || !t.n_ends || !flag || !off || !tmp || !rb || !dctl) {
+  if (!t.label || !t.n_points || !t.t_min || !t.t_max || !t.n_ends || !ts.bits || !ts.cnt || !ts.base || !ts.scan_tmp ||
+      !ts.table || !dctl) {
     ftk_traj_table_free(&t, opt, stream);
     return fail(FTK_ERR_OOM, "trajectory table allocation failed");
   }
   hipError_t he = hipMemsetAsync(dctl, 0, sizeof(Ctl), s);
   if (he == hipSuccess)
     he = ftk::launch_traj_table(n, dims_with_t, (const long long*)r->face_id, (const long long*)r->label, r->pos, nh,
-                                ntr, flag, off, &dctl->total, tmp, (long long*)t.label, rb,
-                                (unsigned long long*)t.n_points, (int*)t.t_min, (int*)t.t_max, t.n_ends,
-                                &dctl->status, s);
+                                ntr, ts, (long long*)t.label, (unsigned long long*)t.n_points, (int*)t.t_min,
+                                (int*)t.t_max, t.n_ends, &dctl->total, &dctl->status, s);
   Ctl h;
   if (he == hipSuccess) {
     st = read_ctl(&h, dctl, s);
@@ -1739,70 +1742,60 @@ ftk_status ftk_traj_order(const ftk_cp_result* r, int32_t n, const int64_t* dims
   hipStream_t s = (hipStream_t)stream;
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
-  const size_t nz = (size_t)(nh > 0 ? nh : 1);
-  int* nb = sc.get<int>(2 * nz);
-  unsigned* seg = sc.get<unsigned>(4 * nz);
-  unsigned char* is_ruler = sc.get<unsigned char>(nz);
-  int* rid = sc.get<int>(nz);
-  int* list = sc.get<int>(nz);
-  int* flag = sc.get<int>(nz);
-  long long* off = sc.get<long long>(nz);
-  long long hB;
-  long long* bstart = sc.get<long long>((size_t)ftk::hit_buckets(n, dims_with_t, nh, &hB) + 1);
-  long long* rb = sc.get<long long>((size_t)ftk::row_buckets(n, dims_with_t) + 1);
-  int* cnt = sc.get<int>((size_t)(ntr > 0 ? ntr : 1));
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(nh > ntr ? nh : ntr));
+  const size_t nz = (size_t)(nh > 0 ? nh : 1), nw = (nz + 63) / 64;
+  ftk::OrderScratch os;
+  os.nb = sc.get<int>(2 * nz);
+  os.bits = sc.get<unsigned long long>(nw);
+  os.cnt = sc.get<int>(nw);
+  os.base = sc.get<long long>(nw);
+  os.points = sc.get<int>((size_t)(ntr > 0 ? ntr : 1));
+  os.hits = sc.get<char>(ftk::order_hits_bytes(n, dims_with_t, nh));
+  os.labels = sc.get<char>(ftk::order_labels_bytes(n, dims_with_t));
+  os.scan_tmp = sc.get<long long>(ftk::scan_tmp_elems((long long)nw > ntr ? (long long)nw : ntr));
   Ctl* dctl = sc.get<Ctl>(1);
-  if (!nb || !seg || !is_ruler || !rid || !list || !flag || !off || !bstart || !rb || !cnt || !tmp || !dctl)
+  if (!os.nb || !os.bits || !os.cnt || !os.base || !os.points || !os.hits || !os.labels || !os.scan_tmp || !dctl)
     return fail(FTK_ERR_OOM, "scratch allocation failed");
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
-  HIP_TRY(ftk::launch_order_setup(n, dims_with_t, (const long long*)r->face_id, (const long long*)r->label, nh,
-                                  (const long long*)tt->label, (const unsigned long long*)tt->n_points, tt->n_ends,
-                                  ntr, nb, seg, is_ruler, rid, list, bstart, rb, flag, off, &dctl->total, cnt,
-                                  (long long*)offsets, tmp, &dctl->status, s));
+  HIP_TRY(ftk::launch_order_setup(n, dims_with_t, (const long long*)r->face_id, nh, (const long long*)tt->label,
+                                  (const unsigned long long*)tt->n_points, tt->n_ends, ntr, os, &dctl->total,
+                                  (long long*)offsets, &dctl->status, s));
   Ctl h;
   st = read_ctl(&h, dctl, s);
   if (st) return st;
   if (h.status) return decode_status(h.status);
-  if (nh > 0) {
-    const long long nr = h.total;
-    const size_t nrz = (size_t)(nr > 0 ? nr : 1);
-    int* st0 = sc.get<int>(8 * nrz);
-    int* st1 = sc.get<int>(8 * nrz);
-    int* act0 = sc.get<int>(nrz);
-    int* act1 = sc.get<int>(nrz);
-    if (!st0 || !st1 || !act0 || !act1) return fail(FTK_ERR_OOM, "scratch allocation failed");
-    HIP_TRY(ftk::launch_order_walk(nb, is_ruler, list, nr, nh, seg, st0, &dctl->status, s));
-    // pointer jumping over the rulers: the reach of every open arm doubles per round, so a path of L rulers closes
-    // within ceil(log2 L) + 2 rounds (one more to copy the final states); an arm that walks past n_hits steps is
-    // closed as an invariant error
-    int* in = st0;
-    int* out = st1;
-    const int* act = nullptr;
-    long long n_act = nr;
-    int* lists[2] = {act0, act1};
-    for (int round = 0; n_act > 0; ++round) {
-      if (round >= 64) return fail(FTK_ERR_INVARIANT, "trajectory walk did not close (internal error)");
-      HIP_TRY(hipMemsetAsync(&dctl->cnt[0], 0, sizeof(unsigned long long), s));
-      int* next = lists[round & 1];
-      HIP_TRY(ftk::launch_order_jump(nb, rid, act, n_act, nh, in, out, next, (unsigned long long*)&dctl->cnt[0],
-                                     &dctl->status, s));
-      st = read_ctl(&h, dctl, s);
-      if (st) return st;
-      if (h.status) return decode_status(h.status);
-      n_act = (long long)h.cnt[0];
-      act = next;
-      int* x = in;
-      in = out;
-      out = x;
-    }
-    HIP_TRY(ftk::launch_order_place(n, dims_with_t, (const long long*)r->label, nh, (const long long*)tt->label, rb,
-                                    (const long long*)offsets, is_ruler, rid, seg, in, (long long*)order,
-                                    &dctl->status, s));
+  if (nh == 0) return FTK_OK;
+  const long long nr = h.total;
+  const size_t nrz = (size_t)(nr > 0 ? nr : 1);
+  int* list = sc.get<int>(nrz);
+  unsigned long long* arms = sc.get<unsigned long long>(2 * nrz);
+  unsigned* act[2] = {sc.get<unsigned>(2 * nrz), sc.get<unsigned>(2 * nrz)};
+  unsigned* place = sc.get<unsigned>(nrz);
+  if (!list || !arms || !act[0] || !act[1] || !place) return fail(FTK_ERR_OOM, "scratch allocation failed");
+  HIP_TRY(ftk::launch_order_walk(os, nr, nh, list, arms, &dctl->status, s));
+  // Pointer jumping over the rulers' arms: the reach of every open arm at least doubles per round, so a path of L rulers
+  // closes within ceil(log2 L) + 1 rounds; an arm that reaches past n_hits steps is closed as an invariant error.
+  const unsigned* open = nullptr;
+  long long n_open = 2 * nr;
+  for (int round = 0; n_open > 0; ++round) {
+    if (round >= 64) return fail(FTK_ERR_INVARIANT, "trajectory walk did not close (internal error)");
+    HIP_TRY(hipMemsetAsync(&dctl->cnt[0], 0, sizeof(unsigned long long), s));
+    unsigned* next = act[round & 1];
+    HIP_TRY(ftk::launch_order_jump(open, n_open, nh, arms, next, &dctl->cnt[0], &dctl->status, s));
+    st = read_ctl(&h, dctl, s);
+    if (st) return st;
+    if (h.status) return decode_status(h.status);
+    n_open = (long long)h.cnt[0];
+    open = next;
   }
+  HIP_TRY(ftk::launch_order_place(n, dims_with_t, (const long long*)r->label, nh, (const long long*)tt->label, ntr,
+                                  (const long long*)offsets, os, list, nr, arms, place, (long long*)order,
+                                  &dctl->cnt[1], &dctl->status, s));
   st = read_ctl(&h, dctl, s);
   if (st) return st;
-  return decode_status(h.status);
+  if (h.status) return decode_status(h.status);
+  if (nr + (long long)h.cnt[1] != nh)
+    return fail(FTK_ERR_INVARIANT, "%lld of %lld points lie on no ordered trajectory", nh - nr - (long long)h.cnt[1], nh);
+  return FTK_OK;
 }
 
 namespace {
@@ -1837,14 +1830,14 @@ ftk_status ftk_traj_smooth_types(const ftk_cp_result* r, const ftk_traj_table* t
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
   const long long nh = r->n_hits;
-  int* head = sc.get<int>((size_t)nh);
-  long long* heads = sc.get<long long>((size_t)nh);
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(nh));
+  const size_t nw = (size_t)((nh + 63) / 64);
+  unsigned long long* start_bits = sc.get<unsigned long long>(nw);
+  long long* start_base = sc.get<long long>(nw);
   Ctl* dctl = sc.get<Ctl>(1);
-  if (!head || !heads || !tmp || !dctl) return fail(FTK_ERR_OOM, "scratch allocation failed");
+  if (!start_bits || !start_base || !dctl) return fail(FTK_ERR_OOM, "scratch allocation failed");
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
   HIP_TRY(ftk::launch_smooth((const long long*)order, (const long long*)offsets, tt->n_ends, tt->n, nh, type_in,
-                             half_window, head, heads, &dctl->total, tmp, type_out, &dctl->status, s));
+                             half_window, start_bits, start_base, type_out, &dctl->status, s));
   Ctl h;
   st = read_ctl(&h, dctl, s);
   if (st) return st;
@@ -1866,23 +1859,24 @@ ftk_status ftk_traj_simplify_types(const ftk_cp_result* r, const ftk_traj_table*
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
   const long long nh = r->n_hits;
-  long long* rot = sc.get<long long>((size_t)(tt->n > 0 ? tt->n : 1));
-  int* flag = sc.get<int>((size_t)nh);
-  long long* run_off = sc.get<long long>((size_t)nh);
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(nh));
-  int* tmin = sc.get<int>((size_t)nh);
-  int* tmax = sc.get<int>((size_t)nh);
-  uint8_t* run_type = sc.get<uint8_t>((size_t)nh);
-  uint8_t* new_type = sc.get<uint8_t>((size_t)nh);
-  int* head = sc.get<int>((size_t)nh);
-  long long* heads = sc.get<long long>((size_t)nh);
+  const size_t nw = (size_t)((nh + 63) / 64), nw1 = (size_t)(nh / 64 + 1);
+  ftk::RunScratch rs;
+  rs.start_bits = sc.get<unsigned long long>(nw);
+  rs.start_base = sc.get<long long>(nw);
+  rs.run_bits = sc.get<unsigned long long>(nw1);
+  rs.run_cnt = sc.get<int>(nw1);
+  rs.run_base = sc.get<long long>(nw1);
+  rs.scan_tmp = sc.get<long long>(ftk::scan_tmp_elems((long long)nw1));
+  rs.t_min = sc.get<int>((size_t)nh);
+  rs.t_max = sc.get<int>((size_t)nh);
+  rs.run_type = sc.get<uint8_t>((size_t)nh);
   Ctl* dctl = sc.get<Ctl>(1);
-  if (!rot || !flag || !run_off || !tmp || !tmin || !tmax || !run_type || !new_type || !head || !heads || !dctl)
+  if (!rs.start_bits || !rs.start_base || !rs.run_bits || !rs.run_cnt || !rs.run_base || !rs.scan_tmp || !rs.t_min ||
+      !rs.t_max || !rs.run_type || !dctl)
     return fail(FTK_ERR_OOM, "scratch allocation failed");
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
   HIP_TRY(ftk::launch_simplify(r->n, r->pos, (const long long*)order, (const long long*)offsets, tt->n_ends, tt->n, nh,
-                               type_in, min_persistence, rot, flag, run_off, head, heads, &dctl->total, tmp, tmin,
-                               tmax, run_type, new_type, type_out, &dctl->status, s));
+                               type_in, min_persistence, rs, &dctl->total, type_out, &dctl->status, s));
   Ctl h;
   st = read_ctl(&h, dctl, s);
   if (st) return st;

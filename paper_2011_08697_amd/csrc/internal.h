@@ -127,11 +127,21 @@ size_t scan_tmp_elems(long long n);
 hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s);
 
 // Trajectory post-processing (post.hip).
+// Bytes of the lookup tables of a call (by vertex or by vertex row).
+size_t traj_table_bytes(int n, const int64_t* dims_with_t, long long n_hits);
+size_t order_hits_bytes(int n, const int64_t* dims_with_t, long long n_hits);
+size_t order_labels_bytes(int n, const int64_t* dims_with_t);
+// Words of 64 hits (ceil(n_hits / 64)): root flags, their counts and scan; table: traj_table_bytes.
+struct TableScratch {
+  unsigned long long* bits;
+  int* cnt;
+  long long *base, *scan_tmp;
+  void* table;
+};
 hipError_t launch_traj_table(int n, const int64_t* dims_with_t, const long long* face_id, const long long* label,
-                             const float* pos, long long n_hits, long long n_traj, int* flag, long long* off,
-                             long long* scan_total, long long* scan_tmp, long long* roots, long long* rb,
-                             unsigned long long* hits, int* t_min, int* t_max, int* n_ends, unsigned* status,
-                             hipStream_t s);
+                             const float* pos, long long n_hits, long long n_traj, const TableScratch& sc,
+                             long long* roots, unsigned long long* hits, int* t_min, int* t_max, int* n_ends,
+                             long long* n_roots, unsigned* status, hipStream_t s);
 hipError_t launch_slice_range(int n, const int64_t* dims_with_t, const long long* face_id, long long n_hits,
                               long long t0, long long* range, hipStream_t s);
 hipError_t launch_slice_compact(int n, const int64_t* dims_with_t, const long long* face_id, long long lo,
@@ -142,31 +152,32 @@ hipError_t launch_filter_loops(const long long* label, long long n_hits, const l
                                uint8_t* keep, hipStream_t s);
 
 // Order of the points along each trajectory.  setup: per-trajectory offsets (offsets[n_traj] = n_hits), cell
-// neighbours nb ([n_hits][2] int32), loop cuts, rulers (is_ruler, rid = slot in list, *n_rulers = count); seg
-// ([n_hits][2] x 2 uint32) is cleared.  walk: ruler-to-ruler walks filling seg, ruler states st ([n_rulers][2] x 4
-// int32).  jump: one pointer-jumping round over the listed rulers (act = null: all), still-open ones appended to
-// next.  place: order[] from the rulers' final states.
-hipError_t launch_order_setup(int n, const int64_t* dims_with_t, const long long* face_id, const long long* label,
-                              long long n_hits, const long long* roots, const unsigned long long* n_points,
-                              const int* n_ends, long long n_traj, int* nb, unsigned* seg, unsigned char* is_ruler,
-                              int* rid, int* list, long long* bstart, long long* rb, int* flag, long long* off,
-                              long long* n_rulers, int* cnt, long long* offsets, long long* scan_tmp, unsigned* status,
-                              hipStream_t s);
-// Number of vertex rows of the grid: the sorted hit and label lookups of the post-processing bucket their face ids
-// by row, so their bucket tables (bstart, rb) need row_buckets() + 1 entries.
-long long row_buckets(int n, const int64_t* dims_with_t);
-// Buckets of the hit lookup of the ordering: one per vertex when the hits are dense (at least one per 16 vertices),
-// else one per row; *B = face ids per bucket.  bstart needs the returned count + 1 entries.
-long long hit_buckets(int n, const int64_t* dims_with_t, long long n_hits, long long* B);
-hipError_t launch_order_walk(const int* nb, const unsigned char* is_ruler, const int* list, long long n_rulers,
-                             long long n_hits, unsigned* seg, int* st, unsigned* status, hipStream_t s);
-hipError_t launch_order_jump(const int* nb, const int* rid, const int* act, long long n_act, long long n_hits,
-                             const int* in, int* out, int* next, unsigned long long* next_n, unsigned* status,
-                             hipStream_t s);
+// neighbours nb ([n_hits][2] int32), loop cuts, ruler flags (words of 64 hits, as in TableScratch; *n_rulers = count).
+// walk: the rulers' hits (list) and the states of their arms (st, 2 n_rulers), from walks to the next rulers.  jump:
+// pointer jumping over the listed arms (act = null: all), still-open ones appended to next.  place: the rulers'
+// positions (place, n_rulers) and order[]; *placed += the hits between the rulers.
+struct OrderScratch {
+  int* nb;
+  unsigned long long* bits;
+  int* cnt;
+  long long* base;
+  int* points;          // [n_traj]
+  void *hits, *labels;  // order_hits_bytes, order_labels_bytes
+  long long* scan_tmp;  // for the words and for n_traj
+};
+hipError_t launch_order_setup(int n, const int64_t* dims_with_t, const long long* face_id, long long n_hits,
+                              const long long* roots, const unsigned long long* n_points, const int* n_ends,
+                              long long n_traj, const OrderScratch& sc, long long* n_rulers, long long* offsets,
+                              unsigned* status, hipStream_t s);
+hipError_t launch_order_walk(const OrderScratch& sc, long long n_rulers, long long n_hits, int* list,
+                             unsigned long long* st, unsigned* status, hipStream_t s);
+hipError_t launch_order_jump(const unsigned* act, long long n_act, long long n_hits, unsigned long long* st,
+                             unsigned* next, unsigned long long* next_n, unsigned* status, hipStream_t s);
 hipError_t launch_order_place(int n, const int64_t* dims_with_t, const long long* label, long long n_hits,
-                              const long long* roots, const long long* rb, const long long* offsets,
-                              const unsigned char* is_ruler, const int* rid, const unsigned* seg, const int* st,
-                              long long* order, unsigned* status, hipStream_t s);
+                              const long long* roots, long long n_traj, const long long* offsets,
+                              const OrderScratch& sc, const int* list, long long n_rulers,
+                              const unsigned long long* st, unsigned* place, long long* order,
+                              unsigned long long* placed, unsigned* status, hipStream_t s);
 // Isovolume tracking (iso.hip).  Words of 64 vertices of a row (ceil(nx / 64) * ny * nz * nt of them) carry the sides
 // (bits) and the counts of crossings, cubes with tetrahedra and runs of equal sides, whose exclusive scans are hbase,
 // abase, rbase; *n_tets += the tetrahedra.
@@ -211,15 +222,25 @@ hipError_t launch_pm_emit(const float* xy, const int* tri, const int* edge, cons
                           const float* field, long long nv, long long nf, long long ne, int nt, float qscale,
                           const unsigned char* flag, const long long* base, long long n_hits, long long* face_id,
                           float* pos, unsigned* parent, unsigned* status, hipStream_t s);
-// Type smoothing and run simplification along an order (head/heads: [n_hits] int / int64 scratch).
+// Type smoothing and run simplification along an order (starts: words of 64 positions, as in RunScratch).
 hipError_t launch_smooth(const long long* order, const long long* offsets, const int* n_ends, long long n_traj,
-                         long long n_hits, const uint8_t* type_in, int half, int* head, long long* heads,
-                         long long* total, long long* scan_tmp, uint8_t* type_out, unsigned* status, hipStream_t s);
+                         long long n_hits, const uint8_t* type_in, int half, unsigned long long* start_bits,
+                         long long* start_base, uint8_t* type_out, unsigned* status, hipStream_t s);
+// Words of 64 positions: trajectory starts (ceil(n_hits / 64)), run starts (one for position n_hits too); bounds and type
+// of the runs (n_hits).
+struct RunScratch {
+  unsigned long long* start_bits;
+  long long* start_base;
+  unsigned long long* run_bits;
+  int* run_cnt;
+  long long *run_base, *scan_tmp;
+  int *t_min, *t_max;
+  uint8_t* run_type;
+};
 hipError_t launch_simplify(int n, const float* pos, const long long* order, const long long* offsets,
                            const int* n_ends, long long n_traj, long long n_hits, const uint8_t* type_in, float theta,
-                           long long* rot, int* flag, long long* run_off, int* head, long long* heads,
-                           long long* total, long long* scan_tmp, int* t_min, int* t_max, uint8_t* run_type,
-                           uint8_t* new_type, uint8_t* type_out, unsigned* status, hipStream_t s);
+                           const RunScratch& sc, long long* n_runs, uint8_t* type_out, unsigned* status,
+                           hipStream_t s);
 
 // Union-find passes over n hits: extra unions from the work list, then labels = face_id of the root.
 hipError_t launch_uf_hook(unsigned* parent, const uint2* work, const unsigned long long* work_count,
