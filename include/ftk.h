@@ -258,8 +258,8 @@ ftk_status ftk_cp_filter_loops(const ftk_cp_result* r, const ftk_traj_table* tt,
  *           label) order, each in curve order.  A path runs from its end with the smaller face id to the other
  *           end; a closed loop starts at its label face and steps first to its neighbour with the smaller face id.
  *   offsets (device, caller-owned, n_trajectories + 1 entries): start of each trajectory in order[], n_hits last.
- * Synchronises the stream once per list-ranking round (at most about log2 of the longest trajectory, usually 2).  FTK_ERR_CAPACITY
- * beyond 2^31 - 1 points; FTK_ERR_INVARIANT if a cell holding a punctured face has no or several other punctured
+ * Synchronises the stream once per list-ranking round (at most about log2 of the longest trajectory, usually 2).
+ * FTK_ERR_CAPACITY beyond 2^31 - 1 points; FTK_ERR_INVARIANT if a cell holding a punctured face has no or several other punctured
  * sides, or a trajectory is not one curve.
  */
 ftk_status ftk_traj_order(const ftk_cp_result* r, int32_t n, const int64_t* dims_with_t, const ftk_traj_table* tt,

@@ -183,9 +183,10 @@ struct Phases {
 // Control block read back by the host.
 struct Ctl {
   unsigned status;   // status bits of the kernels (the streaming form: of its emissions, kept from create to finish)
-  unsigned dstatus;  // status bits of the streaming form's per-push detection (cleared and read by every push)
+  unsigned dstatus;  // status bits of the streaming form's detection of the current step
   long long total;
   unsigned long long cnt[ftk::CNT_N];
+  unsigned taken;    // dstatus of the last detected step
 };
 
 void resolve(const ftk_options* in, ftk_options* o) {
@@ -226,9 +227,50 @@ Alloc make_alloc(const ftk_options& o, hipStream_t s) {
     if (e_ != hipSuccess) return fail(FTK_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_));           \
   } while (0)
 
-ftk_status read_ctl(Ctl* h, const Ctl* d, hipStream_t s) {
-  HIP_TRY(hipMemcpyAsync(h, d, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+// Pinned host slots for the read-backs of the control block: a copy to pageable memory and its synchronisation take
+// 22 us beside 14 for pinned memory.  One allocation of 16 KB per process, made by the first call that reads back; a
+// slot belongs to one call from the copy to the end of the synchronisation, and a call that finds none free (or no pinned
+// memory) copies to its own memory.
+constexpr int kPinSlots = 64;
+constexpr size_t kPinBytes = 256;
+std::mutex g_pin_mu;
+char* g_pin = nullptr;
+bool g_pin_tried = false;
+unsigned long long g_pin_free = ~0ull;
+
+int pin_take() {
+  std::lock_guard<std::mutex> lk(g_pin_mu);
+  if (!g_pin_tried) {
+    g_pin_tried = true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kPinSlots * kPinBytes, hipHostMallocPortable) == hipSuccess)
+      g_pin = (char*)p;
+    else
+      (void)hipGetLastError();
+  }
+  if (!g_pin || !g_pin_free) return -1;
+  const int k = __builtin_ctzll(g_pin_free);
+  g_pin_free &= g_pin_free - 1;
+  return k;
+}
+
+void pin_give(int k) {
+  std::lock_guard<std::mutex> lk(g_pin_mu);
+  g_pin_free |= 1ull << k;
+}
+
+// pinned = false: for calls that must not allocate anything
+ftk_status read_ctl(Ctl* h, const Ctl* d, hipStream_t s, bool pinned = true) {
+  static_assert(sizeof(Ctl) <= kPinBytes, "a slot holds a control block");
+  const int k = pinned ? pin_take() : -1;
+  void* to = k >= 0 ? (void*)(g_pin + k * kPinBytes) : (void*)h;
+  // after an error the copy may still be on its way: the slot is then not used again
+  HIP_TRY(hipMemcpyAsync(to, d, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  if (k >= 0) {
+    std::memcpy(h, to, sizeof(Ctl));
+    pin_give(k);
+  }
   return FTK_OK;
 }
 
@@ -434,6 +476,7 @@ struct Mem2 {
   virtual ftk_status scratch_error(int group, size_t bytes) = 0;
   virtual ftk_status outputs(ftk_cp_result& r, long long nh, unsigned outs) = 0;
   virtual void drop_outputs(ftk_cp_result& r) = 0;
+  virtual bool may_allocate() const { return true; }
 };
 
 // The library's own memory: scratch from the caller's allocator hooks when given, else from the block cache;
@@ -538,7 +581,7 @@ ftk_status track2d_core(const float* field, ftk_field_kind kind, int64_t nx, int
   ph.mark(1);
   HIP_TRY(launch_scan(seg_cnt, seg_off, nseg, &dctl->total, scan_tmp, s));
   ph.mark(2);
-  ftk_status st = read_ctl(&h, dctl, s);
+  ftk_status st = read_ctl(&h, dctl, s, mem.may_allocate());
   if (st) return st;
   const bool wide = (h.status & ST_WIDE) != 0;
   st = decode_status(h.status);
@@ -605,7 +648,7 @@ ftk_status track2d_core(const float* field, ftk_field_kind kind, int64_t nx, int
     mem.drop_outputs(r);
     return fail(FTK_ERR_HIP, "kernel launch: %s", hipGetErrorString(he));
   }
-  st = read_ctl(&h, dctl, s);
+  st = read_ctl(&h, dctl, s, mem.may_allocate());
   if (!st) st = decode_status(h.status);
   if (st) {
     mem.drop_outputs(r);
@@ -691,6 +734,7 @@ struct StaticMem2 : Mem2 {
     return FTK_OK;
   }
   void drop_outputs(ftk_cp_result& r) override { std::memset(&r, 0, sizeof(r)); }  // the caller's arrays
+  bool may_allocate() const override { return false; }
 };
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1046,14 +1090,15 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
 // Streaming (Sec. 3.2 "Ordinal and interval mesh elements": every simplex is visited with a sliding window of two
 // time steps).  2D: the tracker keeps the last three steps in a ring; pushing step s detects the anchors of step
 // s-1 (its ordinal simplices and the interval ones towards s) and emits step s-2, whose +t neighbour masks now
-// exist.  finish() closes the series and runs the global union-find passes.  3D: the steps are accumulated on the
-// device and the one-shot path runs at finish().
+// exist.  finish() closes the series and runs the global union-find passes.  3D: the same schedule.
 // ---------------------------------------------------------------------------------------------------------------
-__global__ void add_plane_base(long long* __restrict__ off, long long n, const long long* __restrict__ running) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) off[i] += *running;
+// Closes a step's detection: its status bits for the read-back, cleared for the next step.
+__global__ void take_status(unsigned* status, unsigned* taken) {
+  if (threadIdx.x == 0) {
+    *taken = *status;
+    *status = 0u;
+  }
 }
-__global__ void bump_running(long long* running, const long long* plane_total) { *running += *plane_total; }
 
 }  // namespace ftk
 
@@ -1078,7 +1123,6 @@ struct ftk_tracker {
   long long* oring = nullptr;
   long long* scan_tmp = nullptr;
   void* dctl = nullptr;
-  long long* dplane = nullptr;
   long long nseg_plane = 0;
   int plane_wide[3] = {0, 0, 0};
   std::vector<long long> total_after;  // hits through step p
@@ -1102,7 +1146,7 @@ static void tracker_free_all(ftk_tracker* h) {
   const Alloc al = tracker_alloc(h);
   (void)hipStreamSynchronize(h->s);
   void* ps[] = {h->fring, h->mring, h->mring3, h->cert3, h->facts3, h->runs3, h->cring, h->oring, h->scan_tmp, h->dctl,
-                h->dplane, h->face_id, h->pos, h->mu, h->type, h->flags, h->parent, h->work};
+                h->face_id, h->pos, h->mu, h->type, h->flags, h->parent, h->work};
   for (void* p : ps) al.put(p);
   h->fring = nullptr;
   h->mring = nullptr;
@@ -1114,7 +1158,6 @@ static void tracker_free_all(ftk_tracker* h) {
   h->oring = nullptr;
   h->scan_tmp = nullptr;
   h->dctl = nullptr;
-  h->dplane = nullptr;
   h->face_id = nullptr;
   h->pos = h->mu = nullptr;
   h->type = h->flags = nullptr;
@@ -1126,7 +1169,7 @@ static void tracker_free_all(ftk_tracker* h) {
 static ftk_status tracker_reserve(ftk_tracker* h, long long need, long long keep) {
   if (need <= h->cap) return FTK_OK;
   const Alloc al = tracker_alloc(h);
-  long long nc = h->cap ? h->cap : 1024;
+  long long nc = h->cap ? h->cap : 16384;
   while (nc < need) nc = nc + nc / 2 + 1024;
   const unsigned outs = h->o.outputs;
   auto grow = [&](void** p, size_t elem, bool want) -> bool {
@@ -1161,6 +1204,9 @@ static ftk_status tracker_reserve(ftk_tracker* h, long long need, long long keep
   return FTK_OK;
 }
 
+// hits through the last detected step
+static long long tracker_total(const ftk_tracker* h) { return h->total_after.empty() ? 0 : h->total_after.back(); }
+
 static Grid2 tracker_grid(ftk_tracker* h, int t_begin, int nt) {
   Grid2 g;
   g.f = h->fring;
@@ -1181,7 +1227,9 @@ static Grid2 tracker_grid(ftk_tracker* h, int t_begin, int nt) {
 
 constexpr int kOpenNt = 1 << 29;  // "series still open": no step is the last one
 
-// Detection + offsets of step p (anchors at p), nt = kOpenNt while open.
+// Detection + offsets of step p (anchors at p), nt = kOpenNt while open: queued here, its outcome taken by
+// tracker_detected after the read-back, so a push of a 2D step synchronises once (500^2 scalar steps: 110 -> 59 us a
+// push; three read-backs to pageable memory, offsets by five launches).
 static ftk_status tracker_detect(ftk_tracker* h, int p, int nt) {
   Ctl* dctl = (Ctl*)h->dctl;
   Grid2 g = tracker_grid(h, p, nt);
@@ -1190,23 +1238,19 @@ static ftk_status tracker_detect(ftk_tracker* h, int p, int nt) {
   long long* off = h->oring + (size_t)slot * h->nseg_plane;
   const long long waves = ((h->nx + 63) / 64) * ((h->ny + kDetectRows - 1) / kDetectRows);
   const int ty = h->o.tile_y ? h->o.tile_y : (waves < 4 * kDetResident ? 8 : 32);
-  HIP_TRY(hipMemsetAsync(&dctl->dstatus, 0, sizeof(unsigned), h->s));
   HIP_TRY(launch_detect2d(g, ty, 1, h->mring, h->cring, &dctl->dstatus, h->s));
-  unsigned st = 0;
-  HIP_TRY(hipMemcpyAsync(&st, &dctl->dstatus, sizeof(unsigned), hipMemcpyDeviceToHost, h->s));
-  HIP_TRY(hipStreamSynchronize(h->s));
-  if (st & (ST_NONFINITE | ST_RANGE)) return decode_status(st);
-  h->plane_wide[slot] = (st & ST_WIDE) ? 1 : 0;
-  HIP_TRY(launch_scan(cnt, off, h->nseg_plane, h->dplane, h->scan_tmp, h->s));
-  add_plane_base<<<(unsigned)((h->nseg_plane + 255) / 256), 256, 0, h->s>>>(off, h->nseg_plane, &dctl->total);
-  bump_running<<<1, 1, 0, h->s>>>(&dctl->total, h->dplane);
-  HIP_TRY(hipGetLastError());
-  long long tot = 0;
-  HIP_TRY(hipMemcpyAsync(&tot, &dctl->total, sizeof(long long), hipMemcpyDeviceToHost, h->s));
-  HIP_TRY(hipStreamSynchronize(h->s));
-  if (tot > 0xFFFFFFFELL) return fail(FTK_ERR_CAPACITY, "%lld punctured simplices exceed 2^32 - 2", tot);
-  h->total_after.push_back(tot);
-  return tracker_reserve(h, tot, h->emitted);
+  take_status<<<1, 64, 0, h->s>>>(&dctl->dstatus, &dctl->taken);
+  HIP_TRY(launch_scan(cnt, off, h->nseg_plane, &dctl->total, h->scan_tmp, h->s, tracker_total(h)));
+  return FTK_OK;
+}
+
+// The outcome of step p's detection, and room for its hits.
+static ftk_status tracker_detected(ftk_tracker* h, int p, const Ctl& c) {
+  if (c.taken & (ST_NONFINITE | ST_RANGE)) return decode_status(c.taken);
+  h->plane_wide[p % 3] = (c.taken & ST_WIDE) ? 1 : 0;
+  if (c.total > 0xFFFFFFFELL) return fail(FTK_ERR_CAPACITY, "%lld punctured simplices exceed 2^32 - 2", c.total);
+  h->total_after.push_back(c.total);
+  return tracker_reserve(h, c.total, h->emitted);
 }
 
 static ftk_status tracker_emit(ftk_tracker* h, int e, int nt) {
@@ -1254,33 +1298,24 @@ static ftk_status tracker_detect3(ftk_tracker* h, int p, int nt) {
   const int slot = p % 3;
   int* cnt = h->cring + (size_t)slot * h->nseg_plane;
   long long* off = h->oring + (size_t)slot * h->nseg_plane;
-  zero_words<<<1, 64, 0, h->s>>>(&dctl->dstatus, 1);
   zero_words<<<1, 64, 0, h->s>>>((unsigned*)&dctl->cnt[CNT_RUNS], 4);  // and CNT_TAKEN
   HIP_TRY(hipGetLastError());
   HIP_TRY(launch_fill_words((unsigned*)cnt, 0u, h->nseg_plane, h->s));
   HIP_TRY(launch_facts3d(g, 1, h->facts3, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->dstatus, h->s));
-  unsigned st = 0;
-  HIP_TRY(launch_detect3d(g, false, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->cnt[CNT_TAKEN], h->mring3, h->cring, &dctl->dstatus, h->s));
-  HIP_TRY(hipMemcpyAsync(&st, &dctl->dstatus, sizeof(unsigned), hipMemcpyDeviceToHost, h->s));
-  HIP_TRY(hipStreamSynchronize(h->s));
-  if (st & (ST_NONFINITE | ST_RANGE)) return decode_status(st);
-  h->plane_wide[slot] = (st & ST_WIDE) ? 1 : 0;
-  if (st & ST_WIDE) {
-    zero_words<<<1, 64, 0, h->s>>>((unsigned*)&dctl->cnt[CNT_TAKEN], 2);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(launch_detect3d(g, true, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->cnt[CNT_TAKEN], h->mring3, h->cring,
+  Ctl c;
+  for (bool wide = false;; wide = true) {
+    HIP_TRY(launch_detect3d(g, wide, h->runs3, &dctl->cnt[CNT_RUNS], &dctl->cnt[CNT_TAKEN], h->mring3, h->cring,
                             &dctl->dstatus, h->s));
+    if (!wide) take_status<<<1, 64, 0, h->s>>>(&dctl->dstatus, &dctl->taken);
+    HIP_TRY(launch_scan(cnt, off, h->nseg_plane, &dctl->total, h->scan_tmp, h->s, tracker_total(h)));
+    ftk_status st = read_ctl(&c, dctl, h->s);
+    if (st) return st;
+    if (wide || !(c.taken & ST_WIDE) || (c.taken & (ST_NONFINITE | ST_RANGE))) break;
+    zero_words<<<1, 64, 0, h->s>>>((unsigned*)&dctl->cnt[CNT_TAKEN], 2);  // values beyond the narrow form: again
   }
-  HIP_TRY(launch_scan(cnt, off, h->nseg_plane, h->dplane, h->scan_tmp, h->s));
-  add_plane_base<<<(unsigned)((h->nseg_plane + 255) / 256), 256, 0, h->s>>>(off, h->nseg_plane, &dctl->total);
-  bump_running<<<1, 1, 0, h->s>>>(&dctl->total, h->dplane);
+  zero_words<<<1, 64, 0, h->s>>>(&dctl->dstatus, 1);
   HIP_TRY(hipGetLastError());
-  long long tot = 0;
-  HIP_TRY(hipMemcpyAsync(&tot, &dctl->total, sizeof(long long), hipMemcpyDeviceToHost, h->s));
-  HIP_TRY(hipStreamSynchronize(h->s));
-  if (tot > 0xFFFFFFFELL) return fail(FTK_ERR_CAPACITY, "%lld punctured simplices exceed 2^32 - 2", tot);
-  h->total_after.push_back(tot);
-  return tracker_reserve(h, tot, h->emitted);
+  return tracker_detected(h, p, c);
 }
 
 static ftk_status tracker_emit3(ftk_tracker* h, int e, int nt) {
@@ -1347,10 +1382,9 @@ extern "C" ftk_status ftk_cp_create(int32_t n, const int64_t* dims, ftk_field_ki
     h->oring = (long long*)al.get(sizeof(long long) * 3 * h->nseg_plane);
     h->scan_tmp = (long long*)al.get(sizeof(long long) * ftk::scan_tmp_elems(h->nseg_plane));
     h->dctl = al.get(sizeof(Ctl));
-    h->dplane = (long long*)al.get(sizeof(long long));
     const bool ring_ok =
         n == 2 ? h->mring != nullptr : (h->mring3 && h->cert3 && h->facts3 && h->runs3);
-    if (!h->fring || !ring_ok || !h->cring || !h->oring || !h->scan_tmp || !h->dctl || !h->dplane) {
+    if (!h->fring || !ring_ok || !h->cring || !h->oring || !h->scan_tmp || !h->dctl) {
       ftk::tracker_free_all(h);
       delete h;
       return fail(FTK_ERR_OOM, "tracker allocation failed");
@@ -1376,17 +1410,21 @@ extern "C" ftk_status ftk_cp_push(ftk_tracker* h, const float* step) {
   HIP_TRY(hipMemcpyAsync(h->fring + (size_t)(s % 3) * h->step_elems, step, bytes, hipMemcpyDeviceToDevice, h->s));
   ftk_status st = FTK_OK;
   if (h->n == 2) {
+    // the emission of step s - 2 reads the masks and offsets of step s - 1, not its status or its room
     if (s >= 1) st = ftk::tracker_detect(h, s - 1, ftk::kOpenNt);
     if (!st && s >= 2) st = ftk::tracker_emit(h, s - 2, ftk::kOpenNt);
+    Ctl c;
+    if (!st) st = read_ctl(&c, (const Ctl*)h->dctl, h->s);  // also: the caller may reuse `step` on return
+    if (!st && s >= 1) st = ftk::tracker_detected(h, s - 1, c);
   } else {
     if (s >= 1) st = ftk::tracker_detect3(h, s - 1, ftk::kOpenNt);
     if (!st && s >= 2) st = ftk::tracker_emit3(h, s - 2, ftk::kOpenNt);
+    if (!st) HIP_TRY(hipStreamSynchronize(h->s));  // the caller may reuse `step` on return
   }
   if (st) {
     h->state = 2;
     return st;
   }
-  HIP_TRY(hipStreamSynchronize(h->s));  // the caller may reuse `step` on return
   ++h->steps;
   return FTK_OK;
 }
@@ -1402,8 +1440,11 @@ extern "C" ftk_status ftk_cp_finish(ftk_tracker* h, ftk_cp_result* out) {
   Ctl* dctl = (Ctl*)h->dctl;
   ftk_status st;
   if (h->n == 2) {
+    Ctl c;
     st = ftk::tracker_detect(h, N - 1, N);
     if (!st) st = ftk::tracker_emit(h, N - 2, N);
+    if (!st) st = read_ctl(&c, dctl, h->s);
+    if (!st) st = ftk::tracker_detected(h, N - 1, c);
     if (!st) st = ftk::tracker_emit(h, N - 1, N);
   } else {
     st = ftk::tracker_detect3(h, N - 1, N);

@@ -124,7 +124,8 @@ hipError_t launch_emit3d(const Grid3& g, bool wide, const uint64_t* masks, const
 // Exclusive scan of n int32 counts into int64 offsets; total written to *total (device).  tmp must hold
 // scan_tmp_elems(n) int64 values.
 size_t scan_tmp_elems(long long n);
-hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s);
+hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s,
+                       long long base = 0);
 
 // Trajectory post-processing (post.hip).
 // Bytes of the lookup tables of a call (by vertex or by vertex row).

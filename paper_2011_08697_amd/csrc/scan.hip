@@ -9,9 +9,14 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kItems = 8;
 constexpr int kTile = kThreads * kItems;
+// Up to this many counts one block scans in rounds of kOneThreads * kItems: three small launches and their gaps cost
+// about 8 us, a round about 2 us and one launch.
+constexpr int kOneThreads = 1024;
+constexpr long long kOneBlock = 2 * kOneThreads * kItems;
 
+template <int THREADS>
 __device__ __forceinline__ long long block_excl_scan(long long v, long long* total) {
-  __shared__ long long wsum[kThreads / kWave];
+  __shared__ long long wsum[THREADS / kWave];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   long long x = v;
 #pragma unroll
@@ -23,7 +28,7 @@ __device__ __forceinline__ long long block_excl_scan(long long v, long long* tot
   __syncthreads();
   long long before = 0, all = 0;
 #pragma unroll
-  for (int i = 0; i < kThreads / kWave; ++i) {
+  for (int i = 0; i < THREADS / kWave; ++i) {
     if (i < w) before += wsum[i];
     all += wsum[i];
   }
@@ -32,8 +37,30 @@ __device__ __forceinline__ long long block_excl_scan(long long v, long long* tot
   return before + x - v;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void scan_reduce(const T* __restrict__ in, long long n,
+__global__ __launch_bounds__(kOneThreads) void scan_one(const int* __restrict__ in, long long* __restrict__ out,
+                                                        long long n, long long base, long long* __restrict__ total) {
+  for (long long b0 = 0; b0 < n; b0 += kOneThreads * kItems) {
+    const long long first = b0 + threadIdx.x * kItems;
+    int v[kItems];
+    long long s = 0;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      v[i] = first + i < n ? in[first + i] : 0;
+      s += v[i];
+    }
+    long long all;
+    long long run = base + block_excl_scan<kOneThreads>(s, &all);
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      if (first + i < n) out[first + i] = run;
+      run += v[i];
+    }
+    base += all;
+  }
+  if (threadIdx.x == 0) *total = base;
+}
+
+__global__ __launch_bounds__(kThreads) void scan_reduce(const int* __restrict__ in, long long n,
                                                         long long* __restrict__ tmp) {
   const long long base = (long long)blockIdx.x * kTile + threadIdx.x * kItems;
   long long s = 0;
@@ -41,27 +68,25 @@ __global__ __launch_bounds__(kThreads) void scan_reduce(const T* __restrict__ in
   for (int i = 0; i < kItems; ++i)
     if (base + i < n) s += in[base + i];
   long long tot;
-  block_excl_scan(s, &tot);
+  block_excl_scan<kThreads>(s, &tot);
   if (threadIdx.x == 0) tmp[blockIdx.x] = tot;
 }
 
 // single block: tmp[0..nb) block sums -> exclusive offsets, total
-__global__ __launch_bounds__(kThreads) void scan_blocks(long long* __restrict__ tmp, long long nb,
+__global__ __launch_bounds__(kThreads) void scan_blocks(long long* __restrict__ tmp, long long nb, long long carry,
                                                         long long* __restrict__ total) {
-  long long carry = 0;
   for (long long b0 = 0; b0 < nb; b0 += kThreads) {
     long long i = b0 + threadIdx.x;
     long long v = i < nb ? tmp[i] : 0;
     long long tot;
-    long long ex = block_excl_scan(v, &tot);
+    long long ex = block_excl_scan<kThreads>(v, &tot);
     if (i < nb) tmp[i] = carry + ex;
     carry += tot;
   }
   if (threadIdx.x == 0) *total = carry;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void scan_down(const T* __restrict__ in, long long* __restrict__ out,
+__global__ __launch_bounds__(kThreads) void scan_down(const int* __restrict__ in, long long* __restrict__ out,
                                                       long long n, const long long* __restrict__ tmp) {
   const long long base = (long long)blockIdx.x * kTile + threadIdx.x * kItems;
   int v[kItems];
@@ -72,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void scan_down(const T* __restrict__ in, 
     s += v[i];
   }
   long long tot;
-  long long run = tmp[blockIdx.x] + block_excl_scan(s, &tot);
+  long long run = tmp[blockIdx.x] + block_excl_scan<kThreads>(s, &tot);
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     if (base + i < n) out[base + i] = run;
@@ -83,20 +108,17 @@ __global__ __launch_bounds__(kThreads) void scan_down(const T* __restrict__ in, 
 
 size_t scan_tmp_elems(long long n) { return (size_t)((n + kTile - 1) / kTile) + 1; }
 
-namespace {
-template <typename T>
-hipError_t scan_any(const T* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s) {
-  long long nb = (n + kTile - 1) / kTile;
-  if (nb == 0) nb = 1;
-  scan_reduce<T><<<(unsigned)nb, kThreads, 0, s>>>(in, n, tmp);
-  scan_blocks<<<1, kThreads, 0, s>>>(tmp, nb, total);
-  scan_down<T><<<(unsigned)nb, kThreads, 0, s>>>(in, out, n, tmp);
+hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s,
+                       long long base) {
+  if (n <= kOneBlock) {
+    scan_one<<<1, kOneThreads, 0, s>>>(in, out, n, base, total);
+    return hipGetLastError();
+  }
+  const long long nb = (n + kTile - 1) / kTile;
+  scan_reduce<<<(unsigned)nb, kThreads, 0, s>>>(in, n, tmp);
+  scan_blocks<<<1, kThreads, 0, s>>>(tmp, nb, base, total);
+  scan_down<<<(unsigned)nb, kThreads, 0, s>>>(in, out, n, tmp);
   return hipGetLastError();
-}
-}  // namespace
-
-hipError_t launch_scan(const int* in, long long* out, long long n, long long* total, long long* tmp, hipStream_t s) {
-  return scan_any<int>(in, out, n, total, tmp, s);
 }
 
 }  // namespace ftk
