@@ -14,7 +14,6 @@
 #include "../../include/ftk.h"
 #include "common.h"
 #include "internal.h"
-#include "offsets16.h"
 
 namespace {
 
@@ -2254,22 +2253,25 @@ ftk_status ftk_track_cp_mesh(const ftk_mesh* m, const float* field, int64_t nt, 
   if (st) return st;
   hipStream_t s = (hipStream_t)stream;
   const long long nv = m->nv, nf = m->nf, ne = m->ne;
-  const long long S = 3 * nf + 2 * ne, NF = S * nt;
+  const long long S = 3 * nf + 2 * ne, NW = (S + 63) / 64 * nt, chunks = (nt + 63) / 64;
   const Alloc al = make_alloc(o, s);
   Scratch sc(al);
-  const long long G = (NF + 15) / 16;  // groups of 16 faces: the offsets keep one base per group
-  unsigned char* flag = sc.get<unsigned char>((size_t)G * 16);
-  int* gsum = sc.get<int>((size_t)G);
-  long long* base = sc.get<long long>((size_t)G);
-  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(G));
+  ftk::PmScratch ps;
+  ps.rows = sc.get<float>((size_t)(2 * nv * nt));
+  ps.edge_signs = sc.get<unsigned long long>((size_t)(2 * ne * chunks));
+  ps.vertex_signs = sc.get<unsigned long long>((size_t)(nv * chunks));
+  ps.bits = sc.get<unsigned long long>((size_t)NW);
+  ps.cnt = sc.get<int>((size_t)NW);
+  ps.base = sc.get<long long>((size_t)NW);
+  long long* tmp = sc.get<long long>(ftk::scan_tmp_elems(NW));
   Ctl* dctl = sc.get<Ctl>(1);
-  float* ft = sc.get<float>((size_t)(2 * nv * nt));
-  if (!flag || !gsum || !base || !tmp || !dctl || !ft) return fail(FTK_ERR_OOM, "scratch allocation failed");
+  if (!ps.rows || !ps.edge_signs || !ps.vertex_signs || !ps.bits || !ps.cnt || !ps.base || !tmp || !dctl)
+    return fail(FTK_ERR_OOM, "scratch allocation failed");
   HIP_TRY(hipMemsetAsync(dctl, 0, sizeof(Ctl), s));
   const float qscale = std::ldexp(1.0f, o.quant_log2);
-  HIP_TRY(ftk::launch_pm_test(m->xy, m->tri, m->edge, m->tri_edge, field, nv, nf, ne, (int)nt, qscale, ft, flag,
-                              &dctl->status, s));
-  HIP_TRY(ftk::launch_group16_bases(flag, NF, false, gsum, base, &dctl->total, tmp, s));
+  HIP_TRY(ftk::launch_pm_test(m->xy, m->tri, m->edge, m->tri_edge, field, nv, nf, ne, (int)nt, qscale, ps,
+                              &dctl->taken, &dctl->status, s));
+  HIP_TRY(ftk::launch_scan(ps.cnt, ps.base, NW, &dctl->total, tmp, s));
   Ctl h;
   st = read_ctl(&h, dctl, s);
   if (st) return st;
@@ -2293,7 +2295,7 @@ ftk_status ftk_track_cp_mesh(const ftk_mesh* m, const float* field, int64_t nt, 
   hipError_t hr = hipSuccess;
   if (nh > 0) {
     hr = ftk::launch_pm_emit(m->xy, m->tri, m->edge, m->tri_edge, m->edge_tri, field, nv, nf, ne, (int)nt, qscale,
-                             flag, base, nh, (long long*)r.face_id, r.pos, parent, &dctl->status, s);
+                             ps, nh, (long long*)r.face_id, r.pos, parent, &dctl->status, s);
     if (hr == hipSuccess)
       hr = ftk::launch_uf_label(parent, (const long long*)r.face_id, (long long*)r.label, nh, dctl->cnt, s);
   }

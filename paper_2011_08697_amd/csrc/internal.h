@@ -210,19 +210,25 @@ hipError_t launch_vx_emit(const float* psi, int nx, int ny, int nz, int nt, floa
                           const unsigned long long* tmask, const unsigned short* before, const int* wcnt,
                           const long long* wbase, long long n_hits, long long* tri_id, float* pos, unsigned* parent,
                           hipStream_t s);
-// Critical points on an extruded triangle mesh (prism.hip): face tests over nt * S faces (flag, allocated to a
-// multiple of 16 bytes), then emission and the tetrahedron unions, with the hit offsets from the group bases of the
-// flags (offsets16.h).
-// ft_scratch: 2 nv nt floats (the field copied vertex-major for the test).
+// Critical points on an extruded triangle mesh (prism.hip): words of 64 faces per step (ceil(S / 64) * nt of them) with
+// their counts, whose scan is base (*suspect: a cleared word of scratch); then emission and the tetrahedron unions.
+struct PmScratch {
+  float* rows;                       // 2 nv nt: the quantised field, vertex-major
+  unsigned long long* edge_signs;    // 2 ne ceil(nt / 64)
+  unsigned long long* vertex_signs;  // nv ceil(nt / 64)
+  unsigned long long* bits;
+  int* cnt;
+  long long* base;
+};
 hipError_t launch_pm_test(const float* xy, const int* tri, const int* edge, const int* tri_edge, const float* field,
-                          long long nv, long long nf, long long ne, int nt, float qscale, float* ft_scratch,
-                          unsigned char* flag, unsigned* status, hipStream_t s);
+                          long long nv, long long nf, long long ne, int nt, float qscale, const PmScratch& sc,
+                          unsigned* suspect, unsigned* status, hipStream_t s);
 // edge_tri: [ne][2] triangles of each edge (-1: none), or null for a mesh with an edge of more than two triangles
 // (the unions then visit every prism).
 hipError_t launch_pm_emit(const float* xy, const int* tri, const int* edge, const int* tri_edge, const int* edge_tri,
                           const float* field, long long nv, long long nf, long long ne, int nt, float qscale,
-                          const unsigned char* flag, const long long* base, long long n_hits, long long* face_id,
-                          float* pos, unsigned* parent, unsigned* status, hipStream_t s);
+                          const PmScratch& sc, long long n_hits, long long* face_id, float* pos, unsigned* parent,
+                          unsigned* status, hipStream_t s);
 // Type smoothing and run simplification along an order (starts: words of 64 positions, as in RunScratch).
 hipError_t launch_smooth(const long long* order, const long long* offsets, const int* n_ends, long long n_traj,
                          long long n_hits, const uint8_t* type_in, int half, unsigned long long* start_bits,

@@ -1,5 +1,5 @@
-// uf_cached.h -- union for passes that unite many pairs which are mostly connected already (the pentachoron passes
-// of isovolume and vortex surface tracking).
+// uf_cached.h -- union for passes that unite many pairs which are mostly connected already (the runs of isovolume
+// tracking, the cells of vortex surfaces and of extruded meshes).
 #pragma once
 
 #include "common.h"
