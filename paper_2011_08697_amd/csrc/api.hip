@@ -627,9 +627,7 @@ ftk_status track2d_core(const float* field, ftk_field_kind kind, int64_t nx, int
   if (nh > 0) {
     const bool sparse = sparse_emission(g, nh, V);
     if (sparse) {
-      he = launch_fill_words(parent, 0xFFFFFFFFu, nh, s);
-      if (he == hipSuccess)
-        he = launch_emit2d_sparse(g, wide, masks, seg_cnt, seg_off, od, &dctl->status, dctl->cnt, s);
+      he = launch_emit2d_sparse(g, wide, masks, seg_cnt, seg_off, nh, od, &dctl->status, dctl->cnt, s);
     } else {
       he = launch_emit2d(g, wide, emit_steps(g), masks, seg_cnt, seg_off, od, &dctl->status, dctl->cnt, s);
     }
@@ -970,27 +968,28 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
   unsigned* parent = sc.get<unsigned>((size_t)total);
   uint2* work = sc.get<uint2>((size_t)total * 2);
   unsigned* dgb = sc.get<unsigned>((size_t)nser + 1);
-  long long* dpb = sc.get<long long>((size_t)nser + 1);
+  long long* dpb = sc.get<long long>(2 * ((size_t)nser + 1));
   if (!parent || !work || !dgb || !dpb) return fail(FTK_ERR_OOM, "scratch allocation failed");
-  // emission form per series: tiled items (pre_e) for the dense ones, 64-segment blocks (pre_b) for the sparse ones
-  std::vector<long long> pre_b(nser + 1);
+  // emission form per series: tiled items (pre_e) for the dense ones, blocks of 64 segments and of 64 hits
+  // (pre_b, one after the other) for the sparse ones
+  std::vector<long long> pre_b(2 * (nser + 1));
   std::vector<char> sparse(nser);
-  pre_b[0] = 0;
+  long long* pre_h = pre_b.data() + nser + 1;
+  pre_b[0] = pre_h[0] = 0;
   for (int i = 0; i < nser; ++i) {
     const Grid2& g = ser[i].g;
     sparse[i] = sparse_emission(g, bases[i + 1] - bases[i], (long long)g.nx * g.ny * g.nt) ? 1 : 0;
     const int items = pre_e[i + 1] - pre_e[i];
     pre_e[i + 1] = pre_e[i] + (sparse[i] ? 0 : items);
     pre_b[i + 1] = pre_b[i] + (sparse[i] ? ((long long)g.nt * g.ny * g.nxt + 63) / 64 : 0);
+    pre_h[i + 1] = pre_h[i] + (sparse[i] ? (bases[i + 1] - bases[i] + 63) / 64 : 0);
   }
-  // link slots of the sparse series (one per global hit index; cleared when tiled series leave some unwritten) and
-  // their parents' initial value
+  // link slots of the sparse series (one per global hit index; cleared when tiled series leave some unwritten)
   uint2* slots = nullptr;
   if (pre_b[nser] > 0) {
     slots = sc.get<uint2>((size_t)total);
     if (!slots) return fail(FTK_ERR_OOM, "scratch allocation failed");
     if (pre_e[nser] > 0) HIP_TRY(hipMemsetAsync(slots, 0, sizeof(uint2) * (size_t)total, s));
-    HIP_TRY(hipMemsetAsync(parent, 0xFF, sizeof(unsigned) * (size_t)total, s));
   }
   std::vector<unsigned> gb(nser + 1);
   const unsigned outs_mask = o.outputs;
@@ -1034,7 +1033,7 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
   HIP_TRY(hipMemcpyAsync(dser, ser.data(), sizeof(Series2) * nser, hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(dgb, gb.data(), sizeof(unsigned) * (nser + 1), hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(dpre + nser + 1, pre_e.data(), sizeof(int) * (nser + 1), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(dpb, pre_b.data(), sizeof(long long) * (nser + 1), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemcpyAsync(dpb, pre_b.data(), sizeof(long long) * 2 * (nser + 1), hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemsetAsync(dctr, 0, sizeof(int) * 4, s));
   ph.mark(3);
   hipError_t he = hipSuccess;
@@ -1043,7 +1042,8 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
       he = launch_emit2d_batched(dser, dpre + nser + 1, nser, pre_e[nser], wide, dctr, &dctl->status,
                                  &dctl->cnt[CNT_WORK], s);
     if (he == hipSuccess && pre_b[nser] > 0)
-      he = launch_emit2d_sparse_batched(dser, dpb, nser, pre_b[nser], wide, &dctl->status, s);
+      he = launch_emit2d_sparse_batched(dser, dpb, dpb + nser + 1, dgb, nser, pre_b[nser], pre_h[nser], wide,
+                                        &dctl->status, s);
     ph.mark(4);
     if (he == hipSuccess && slots) he = launch_uf_compress(parent, total, s);
     if (he == hipSuccess && pre_e[nser] > 0) he = launch_uf_hook(parent, work, &dctl->cnt[CNT_WORK], 2 * total, s);

@@ -739,7 +739,7 @@ __device__ __forceinline__ void hit_record2(const Grid2& g, const Out2& o, const
   }
   const long long agid = (long long)t * plane + (long long)y * g.nx + ax;
   const size_t oi = idx - o.gbase;
-  o.face_id[oi] = agid * 12 + ty;
+  if (o.face_id) o.face_id[oi] = agid * 12 + ty;  // null: listed already
   if (o.pos) {
     o.pos[oi * 3 + 0] = pos[0];
     o.pos[oi * 3 + 1] = pos[1];
@@ -1329,38 +1329,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Sparse emission: one wavefront per non-empty row segment, with no workgroup barriers.  When hits are rare (a few
-// per thousand vertices) the tile-marching emission above pays a fixed cost per tile and step (ring loads, scans
-// and barriers for a handful of hits).  Here a wavefront reads only what its segment's hits need: the hit masks of
-// the five rows that hold the other sides of their cells (steps t-1..t+1 along y = const, rows y-1..y+1 at step
-// t), the first-hit offsets of the three rows that can hold smaller partners (a partner with a smaller face id has
-// an anchor at t-1, y-1, x-1 or at the same anchor), and the field values of each hit vertex's stencils, gathered
-// through the caches.  No counter is shared: every link joins a hit to a smaller partner, so a hit with one or two
-// smaller partners takes the first as its union-find parent (the parents then point to smaller indices and form a
-// forest whose trees are connected parts of a trajectory; a tree's root is a hit with no smaller partner), and a
-// hit with two writes the second to its own slot of the link array ((i, i) when absent), united afterwards by
-// uf_hook_slots.  A trajectory is a path or a loop of hits (each lies in at most two cells), so the slot links
-// (one per local maximum of the index along it) join all its trees.  To keep the trees shallow, a hit takes its
-// partner's parent instead of the partner when that one is already written (parents start as 0xFFFFFFFF).  The
-// records are the same operations as in the tiled form (hit_record2), so both forms give identical outputs.
+// Sparse emission, for hits that are rare (a few per thousand vertices), where the tile-marching emission above pays a
+// fixed cost per tile and step (ring loads, scans and barriers for a handful of hits).  Two launches: emit2d_ids lists the
+// face ids from the masks of the non-empty row segments (straight into the result), and the hits are then taken a
+// lane each, in full wavefronts.  A hit reads what it needs through the caches: its vertices' stencils, the masks of
+// the anchors that hold the other sides of its cells, and a smaller partner's index by searching the partner's
+// segment in the listed ids.  (A wavefront per segment, with its few hits in its lanes, waited a chain of loads per
+// segment: vector 4096^2 x 50 780 -> 160 us, batch of 12 784 -> 183 us.)  No counter is shared: every link joins a
+// hit to a smaller partner, so a hit with one or two smaller partners takes the first as its union-find parent (the
+// parents then point to smaller indices and form a forest whose trees are connected parts of a trajectory; a tree's
+// root is a hit with no smaller partner), and a hit with two writes the second to its own slot of the link array
+// ((i, i) when absent), united afterwards by uf_hook_slots.  A trajectory is a path or a loop of hits (each lies in at
+// most two cells), so the slot links (one per local maximum of the index along it) join all its trees.  The records are
+// the same operations as in the tiled form (hit_record2), so both forms give identical outputs.
 // ---------------------------------------------------------------------------------------------------------------
 namespace {
-
-constexpr int kSpW = TX + 2;  // anchors x0-1 .. x0+64
-
-// Per-wavefront LDS of the sparse emission.
-struct SparseWave {
-  unsigned short m[5][kSpW];       // hit masks: rows (t, y), (t, y-1), (t, y+1), (t-1, y), (t+1, y)
-  short x[3][kSpW];                // first hit of each anchor relative to its segment: rows (t,y), (t,y-1), (t-1,y)
-  unsigned b[3];                   // first hit index of the segments of those rows
-  unsigned short map[12 * TX];     // hit j of the segment -> anchor lane | type << 6
-  unsigned cof[24];                // triangle side words (Tri2Words), read per hit with a lane-dependent type
-};
-
-// mask row of each neighbour slot, and its offset row (-1: the row only holds larger partners)
-__device__ __forceinline__ int sp_row(int slot) {
-  return slot <= NB_PX ? 0 : (slot == NB_MY ? 1 : (slot == NB_PY ? 2 : (slot == NB_MT ? 3 : 4)));
-}
 
 // Binary32 vector of vertex (x, y) of field plane P (gradient of a scalar by the stencil of pass 1, or the vector
 // itself) and its Jacobian stencil J: the same operations as the staged form.  Coordinates outside the grid are
@@ -1403,137 +1386,104 @@ __device__ __forceinline__ void vertex_stencil2(const Grid2& g, int x, int y, in
   J[3] = diff3(yl.y, v.y, yh.y, y, ny);
 }
 
-// One row segment (anchors x0 .. x0+63 of row y, step t) with `total` hits from global index `base`.
+// a / b of indices: the 64-bit division is a long instruction sequence, so values of 32 bits take the short one
+__device__ __forceinline__ long long index_div(long long a, int b) {
+  if ((a >> 32) == 0) return (unsigned)a / (unsigned)b;
+  return a / b;
+}
+
+// Hit idx, its face id listed.
 template <bool WIDE>
-__device__ __forceinline__ void emit2d_segment(const Grid2& g, int t, int y, int bx, const uint16_t* __restrict__ masks,
-                                               const long long* __restrict__ seg_off, const Out2& o, SparseWave& W,
-                                               unsigned& st,
-                                               unsigned long long& n_fp64, unsigned long long& n_deg,
-                                               unsigned long long& n_linked) {
-  const int lane = lane_id();
-  const int nx = g.nx, ny = g.ny, nt = g.nt, nxt = g.nxt;
-  const int x0 = bx * TX;
-  const bool vector = g.kind != 0;
-  // the five mask rows (clamped addresses: all loads in flight together; cells outside the grid zeroed after)
-  constexpr int NR = (5 * kSpW + 63) / 64;
-  unsigned short mv[NR];
-  bool in[NR];
+__device__ __forceinline__ void emit2d_hit(const Grid2& g, unsigned idx, const unsigned* cof,
+                                           const uint16_t* __restrict__ masks, const int* __restrict__ seg_cnt,
+                                           const long long* __restrict__ seg_off, const Out2& o, unsigned& st,
+                                           unsigned long long& n_fp64, unsigned long long& n_deg,
+                                           unsigned long long& n_linked) {
+  const int nx = g.nx, ny = g.ny, nt = g.nt;
+  const long long* ids = o.face_id - o.gbase;  // by hit index
+  const long long own = ids[idx], v = own / 12, row = index_div(v, nx);
+  const int ty = (int)(own - v * 12), ax = (int)(v - row * nx), t = (int)index_div(row, ny), y = (int)(row - (long long)t * ny);
+  const unsigned w0 = cof[2 * ty], w1 = cof[2 * ty + 1];
+  const unsigned pk = w0 >> 25;
+  const int m1 = pk & 15, m2 = pk >> 4;
+  const int dx1 = m1 & 1, dy1 = (m1 >> 1) & 1, dt1 = (m1 >> 2) & 1;
+  const int dx2 = dx1 + (m2 & 1), dy2 = dy1 + ((m2 >> 1) & 1), dt2 = dt1 + ((m2 >> 2) & 1);
+  const int dxs[3] = {0, dx1, dx2}, dys[3] = {0, dy1, dy2}, dts[3] = {0, dt1, dt2};
+
+  // links (Alg. 1 pass 2): the other punctured side of each tetrahedron holding the triangle; the larger end of each
+  // link records it
+  unsigned sm[2] = {0, 0};
+  int ns = 0;
+  bool bad = false;
+  long long other[2] = {-1, -1};   // smaller partner of the cell
+  long long seg[2] = {0, 0};       // and its row segment
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int e = lane + 64 * i;
-    const int r = e / kSpW, c = e - r * kSpW;
-    const int tt = t + (r == 3 ? -1 : (r == 4 ? 1 : 0));
-    const int yy = y + (r == 1 ? -1 : (r == 2 ? 1 : 0));
-    const int xx = x0 - 1 + c;
-    in[i] = e < 5 * kSpW && tt >= 0 && tt < nt && yy >= 0 && yy < ny && xx >= 0 && xx < nx;
-    const int tc = min(max(tt, 0), nt - 1), yc = min(max(yy, 0), ny - 1), xc = min(max(xx, 0), nx - 1);
-    mv[i] = masks[((long long)mpl(g, tc) * ny + yc) * nx + xc];
-  }
-  unsigned bv = 0;
-  if (lane < 3) {
-    const int tt = lane == 2 ? t - 1 : t, yy = lane == 1 ? y - 1 : y;
-    bv = (unsigned)seg_off[((long long)mpl(g, max(tt, 0)) * ny + max(yy, 0)) * nxt + bx];
-    if (tt < 0 || yy < 0) bv = 0u;
-  }
-  wave_lds_sync();  // the previous segment's reads of W are done
+  for (int k = 0; k < 2; ++k) {
+    const unsigned w = k == 0 ? w0 : w1;
+    const int rule = w & 3, axis = (w >> 2) & 3;
+    const int pa = axis == 0 ? ax : (axis == 1 ? y : t);
+    const int Na = axis == 0 ? nx : (axis == 1 ? ny : nt);
+    const bool exists = !((rule == 2 && pa < 1) || (rule == 3 && pa + 1 > Na - 1));
+    int found = 0;
+    long long id = -1, sg = 0;
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int e = lane + 64 * i;
-    if (e < 5 * kSpW) (&W.m[0][0])[e] = in[i] ? mv[i] : (unsigned short)0;
+    for (int sdx = 0; sdx < 3; ++sdx) {
+      const unsigned f = (w >> (4 + 7 * sdx)) & 127u;
+      const int slot = f & 7, tt = f >> 3;
+      const int xx = ax + (slot == NB_MX ? -1 : (slot == NB_PX ? 1 : 0));
+      const int yy = y + (slot == NB_MY ? -1 : (slot == NB_PY ? 1 : 0));
+      const int ts = t + (slot == NB_MT ? -1 : (slot == NB_PT ? 1 : 0));
+      const bool in = xx >= 0 && xx < nx && yy >= 0 && yy < ny && ts >= 0 && ts < nt;
+      // without a branch, so that the loads are in flight together: outside the grid the own mask is read
+      const long long mr = in ? (long long)mpl(g, ts) * ny + yy : (long long)mpl(g, t) * ny + y;
+      const unsigned um = masks[mr * nx + (in ? xx : ax)];
+      const bool hit = in && ((um >> tt) & 1u);
+      found += hit ? 1 : 0;
+      id = hit ? (((long long)ts * ny + yy) * nx + xx) * 12 + tt : id;
+      sg = hit ? mr * g.nxt + (xx >> 6) : sg;
+    }
+    bad = bad || (exists && found != 1);
+    const bool take = exists && found == 1 && id < own;
+    other[k] = take ? id : -1;
+    seg[k] = sg;
   }
-  if (lane < 3) W.b[lane] = bv;
-  wave_lds_sync();
-  unsigned total = 0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (other[k] < 0) continue;
+    unsigned lo = (unsigned)seg_off[seg[k]], hi = lo + (unsigned)seg_cnt[seg[k]];
+    while (hi - lo > 1) {  // last id of the segment not above the partner's
+      const unsigned mid = (lo + hi) >> 1;
+      if (ids[mid] <= other[k])
+        lo = mid;
+      else
+        hi = mid;
+    }
+    if (ns == 0)
+      sm[0] = lo;
+    else
+      sm[1] = lo;
+    ++ns;
+  }
+  if (bad || t == g.debug_step) st |= ST_INVARIANT;
+  n_linked += ns;
+  o.parent[idx] = ns > 0 ? sm[0] : idx;
+  o.work[idx] = make_uint2(idx, ns > 1 ? sm[1] : idx);
+
+  float qf[3][2];
+  float J[3][4];
+  bool wide = false;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    const int r = i == 2 ? 3 : i;
-    const unsigned c = __popc((unsigned)W.m[r][1 + lane]);
-    const unsigned incl = wave_incl_scan(c);
-    W.x[i][1 + lane] = (short)(incl - c);
-    if (lane == 63) W.x[i][kSpW - 1] = (short)incl;
-    if (lane == 0) W.x[i][0] = (short)(-(int)__popc((unsigned)W.m[r][0]));
-    if (i == 0) total = (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
+    float2 u;
+    vertex_stencil2(g, ax + dxs[i], y + dys[i], t + dts[i], u, J[i]);
+    qf[i][0] = quant(u.x, g.qscale);
+    qf[i][1] = quant(u.y, g.qscale);
+    if constexpr (WIDE)
+      if (!(fabsf(qf[i][0]) < 2147483648.0f) || !(fabsf(qf[i][1]) < 2147483648.0f)) wide = true;
   }
-  {
-    unsigned m = W.m[0][1 + lane];
-    unsigned k = (unsigned)(W.x[0][1 + lane]);
-    while (m) {
-      const unsigned ty = (unsigned)__ffs((int)m) - 1u;
-      m &= m - 1u;
-      W.map[k++] = (unsigned short)((unsigned)lane | (ty << 6));
-    }
-  }
-  wave_lds_sync();
-  const unsigned base = W.b[0];
-  for (unsigned j = lane; j < total; j += 64) {
-    const unsigned ent = W.map[j];
-    const int L = (int)(ent & 63u), ty = (int)(ent >> 6);
-    const unsigned idx = base + j;
-    const int ax = x0 + L;
-    const unsigned w0 = W.cof[2 * ty], w1 = W.cof[2 * ty + 1];
-    const unsigned pk = w0 >> 25;
-    const int m1 = pk & 15, m2 = pk >> 4;
-    const int dx1 = m1 & 1, dy1 = (m1 >> 1) & 1, dt1 = (m1 >> 2) & 1;
-    const int dx2 = dx1 + (m2 & 1), dy2 = dy1 + ((m2 >> 1) & 1), dt2 = dt1 + ((m2 >> 2) & 1);
-    const int dxs[3] = {0, dx1, dx2}, dys[3] = {0, dy1, dy2}, dts[3] = {0, dt1, dt2};
-    float qf[3][2];
-    float J[3][4];
-    bool wide = false;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      float2 v;
-      vertex_stencil2(g, ax + dxs[i], y + dys[i], t + dts[i], v, J[i]);
-      qf[i][0] = quant(v.x, g.qscale);
-      qf[i][1] = quant(v.y, g.qscale);
-      if constexpr (WIDE)
-        if (!(fabsf(qf[i][0]) < 2147483648.0f) || !(fabsf(qf[i][1]) < 2147483648.0f)) wide = true;
-    }
-    hit_record2<WIDE>(g, o, qf, J, wide, vector, ax, y, t, ty, dx1, dy1, dt1, dx2, dy2, dt2, idx, n_fp64, n_deg);
-
-    // links (Alg. 1 pass 2): the other punctured side of each tetrahedron holding the triangle; the larger end of
-    // each link records it
-    unsigned sm0 = 0, sm1 = 0;
-    int ns = 0;
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const unsigned w = k == 0 ? w0 : w1;
-      const int rule = w & 3, axis = (w >> 2) & 3;
-      const int pa = axis == 0 ? ax : (axis == 1 ? y : t);
-      const int Na = axis == 0 ? nx : (axis == 1 ? ny : nt);
-      const bool exists = !((rule == 2 && pa < 1) || (rule == 3 && pa + 1 > Na - 1));
-      int found = 0;
-      unsigned other = 0;
-#pragma unroll
-      for (int sdx = 0; sdx < 3; ++sdx) {
-        const unsigned f = (w >> (4 + 7 * sdx)) & 127u;
-        const int slot = f & 7, tt = f >> 3;
-        const int row = sp_row(slot);
-        const int col = L + 1 + (slot == NB_MX ? -1 : (slot == NB_PX ? 1 : 0));
-        const unsigned um = W.m[row][col];
-        const unsigned hit = (um >> tt) & 1u;
-        const int xr = row == 0 ? 0 : (row == 1 ? 1 : (row == 3 ? 2 : -1));
-        const unsigned cand = xr < 0 ? 0xFFFFFFFFu
-                                     : W.b[xr] + (unsigned)(int)W.x[xr][col] + __popc(um & ((1u << tt) - 1u));
-        found += (int)hit;
-        other = hit ? cand : other;
-      }
-      bad = bad || (exists && found != 1);
-      const bool take = exists && found == 1 && other < idx;
-      sm1 = (take && ns == 1) ? other : sm1;
-      sm0 = (take && ns == 0) ? other : sm0;
-      ns += take ? 1 : 0;
-    }
-    if (bad || t == g.debug_step) st |= ST_INVARIANT;
-    n_linked += ns;
-    unsigned par = idx;
-    if (ns > 0) {  // an ancestor of the partner if already written (a stale read only gives a deeper tree)
-      const unsigned q = __hip_atomic_load(o.parent + sm0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      par = q == 0xFFFFFFFFu ? sm0 : q;
-    }
-    __hip_atomic_store(o.parent + idx, par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    o.work[idx] = make_uint2(idx, ns > 1 ? sm1 : idx);
-  }
+  Out2 rest = o;
+  rest.face_id = nullptr;
+  hit_record2<WIDE>(g, rest, qf, J, wide, g.kind != 0, ax, y, t, ty, dx1, dy1, dt1, dx2, dy2, dt2, idx, n_fp64, n_deg);
 }
 
 // Per-wavefront counters into the call's (or series') counters.
@@ -1548,14 +1498,12 @@ __device__ __forceinline__ void sparse_flush_counts(unsigned long long* cnt, uns
   n_fp64 = n_deg = n_linked = 0;
 }
 
-// Segments [64 blk, 64 blk + 64) of the steps [t_begin, t_end): each lane reads one segment's count, the wavefront
-// walks the non-empty ones.
-template <bool WIDE>
-__device__ __forceinline__ void emit2d_sparse_block(const Grid2& g, long long blk, const uint16_t* __restrict__ masks,
-                                                    const int* __restrict__ seg_cnt,
-                                                    const long long* __restrict__ seg_off, const Out2& o,
-                                                    SparseWave& W, unsigned& st, unsigned long long& n_fp64,
-                                                    unsigned long long& n_deg, unsigned long long& n_linked) {
+// Face ids of the hits of segments [64 blk, 64 blk + 64) of the steps [t_begin, t_end): each lane reads one segment's
+// count, the wavefront walks the non-empty ones, kIdsBatch mask rows in flight.
+constexpr int kIdsBatch = 4;
+__device__ __forceinline__ void emit2d_ids_block(const Grid2& g, long long blk, const uint16_t* __restrict__ masks,
+                                                 const int* __restrict__ seg_cnt,
+                                                 const long long* __restrict__ seg_off, const Out2& o) {
   const unsigned per_step = (unsigned)g.ny * (unsigned)g.nxt;  // segments per step
   const long long nseg = (long long)(g.t_end - g.t_begin) * per_step;
   const long long s0 = blk * 64;
@@ -1572,49 +1520,76 @@ __device__ __forceinline__ void emit2d_sparse_block(const Grid2& g, long long bl
     t += g.t_begin;
   };
   int c = 0;
+  unsigned first = 0;
   if (s0 + lane_id() < nseg) {
     int t;
     unsigned r;
     locate(lane_id(), t, r);
-    c = seg_cnt[(long long)mpl(g, t) * per_step + r];
+    const long long k = (long long)mpl(g, t) * per_step + r;
+    c = seg_cnt[k];
+    first = (unsigned)seg_off[k];
   }
   unsigned long long bal = __ballot(c > 0);
   while (bal) {
-    const int b = __ffsll((long long)bal) - 1;
-    bal &= bal - 1ull;
-    int t;
-    unsigned r;
-    locate(b, t, r);
-    const int y = (int)(r / (unsigned)g.nxt), bx = (int)(r - (unsigned)y * (unsigned)g.nxt);
-    emit2d_segment<WIDE>(g, t, y, bx, masks, seg_off, o, W, st, n_fp64, n_deg, n_linked);
+    unsigned m[kIdsBatch], base[kIdsBatch];
+    long long id0[kIdsBatch];
+#pragma unroll
+    for (int q = 0; q < kIdsBatch; ++q) {
+      m[q] = 0;
+      base[q] = 0;
+      id0[q] = 0;
+      if (bal) {
+        const int b = __ffsll((long long)bal) - 1;
+        bal &= bal - 1ull;
+        int t;
+        unsigned r;
+        locate(b, t, r);
+        const int y = (int)(r / (unsigned)g.nxt), bx = (int)(r - (unsigned)y * (unsigned)g.nxt);
+        const int x = bx * TX + lane_id();
+        const unsigned mv = masks[((long long)mpl(g, t) * g.ny + y) * g.nx + min(x, g.nx - 1)];
+        m[q] = x < g.nx ? mv : 0u;
+        base[q] = (unsigned)__builtin_amdgcn_readlane((int)first, b);
+        id0[q] = (((long long)t * g.ny + y) * g.nx + x) * 12;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kIdsBatch; ++q) {
+      const unsigned n = __popc(m[q]), incl = wave_incl_scan(n);
+      unsigned k = base[q] + incl - n - o.gbase;
+      for (unsigned w = m[q]; w; w &= w - 1u) o.face_id[k++] = id0[q] + __ffs((int)w) - 1;
+    }
   }
 }
 
-// Wavefronts of the sparse emission: enough for four per SIMD.  A wavefront takes one 64-segment block per turn, so
-// the blocks in flight span about 4096 x 64 segments (a few steps at most): the partners at step t-1 of a hit are
-// then mostly written already, which keeps the parent trees shallow.
-constexpr int kSparseWaves = 4096;
+// Wavefronts of the id lists: enough for eight per SIMD.
+constexpr int kSparseWaves = 8192;
 
 }  // namespace
 
-template <bool WIDE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void emit2d_sparse(Grid2 g, const uint16_t* __restrict__ masks,
-                                                     const int* __restrict__ seg_cnt,
-                                                     const long long* __restrict__ seg_off, Out2 o,
-                                                     unsigned* __restrict__ status,
-                                                     unsigned long long* __restrict__ cnt) {
-  __shared__ SparseWave sw[4];
-  __shared__ unsigned long long red[3][4];
-  SparseWave& W = sw[threadIdx.x >> 6];
-  if ((threadIdx.x & 63) < 24) W.cof[threadIdx.x & 63] = kTri2WordsDev.w[threadIdx.x & 63];
-  wave_lds_sync();
+__global__ __launch_bounds__(256) void emit2d_ids(Grid2 g, const uint16_t* __restrict__ masks,
+                                                  const int* __restrict__ seg_cnt,
+                                                  const long long* __restrict__ seg_off, Out2 o) {
   const long long nblk = ((long long)(g.t_end - g.t_begin) * g.ny * g.nxt + 63) / 64;
   const long long nw = (long long)gridDim.x * 4;
-  unsigned st = 0;
-  unsigned long long n_fp64 = 0, n_deg = 0, n_linked = 0;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // wave-uniform: scalar loop state
   for (long long blk = (long long)blockIdx.x * 4 + wv; blk < nblk; blk += nw)
-    emit2d_sparse_block<WIDE>(g, blk, masks, seg_cnt, seg_off, o, W, st, n_fp64, n_deg, n_linked);
+    emit2d_ids_block(g, blk, masks, seg_cnt, seg_off, o);
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(256) void emit2d_sparse(Grid2 g, const uint16_t* __restrict__ masks,
+                                                     const int* __restrict__ seg_cnt,
+                                                     const long long* __restrict__ seg_off, long long n_hits, Out2 o,
+                                                     unsigned* __restrict__ status,
+                                                     unsigned long long* __restrict__ cnt) {
+  __shared__ unsigned cof[24];
+  __shared__ unsigned long long red[3][4];
+  if (threadIdx.x < 24) cof[threadIdx.x] = kTri2WordsDev.w[threadIdx.x];
+  __syncthreads();
+  unsigned st = 0;
+  unsigned long long n_fp64 = 0, n_deg = 0, n_linked = 0;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n_hits; i += (long long)gridDim.x * 256)
+    emit2d_hit<WIDE>(g, (unsigned)i, cof, masks, seg_cnt, seg_off, o, st, n_fp64, n_deg, n_linked);
   // one counter update per workgroup (same-address atomics serialise)
   const int w = threadIdx.x >> 6;
   const unsigned long long a = wave_sum64(n_fp64), b = wave_sum64(n_deg), c = wave_sum64(n_linked);
@@ -1695,39 +1670,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 
   }
 }
 
-// Batched sparse emission: the 64-segment blocks of the series that take the sparse form, concatenated (bprefix:
-// per-series block prefix, zero blocks for the others); a wavefront's block -> series by binary search.
-template <bool WIDE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void emit2d_sparse_batched(const Series2* __restrict__ S,
-                                                             const long long* __restrict__ bprefix, int nser,
-                                                             unsigned* status) {
-  __shared__ SparseWave sw[4];
-  SparseWave& W = sw[threadIdx.x >> 6];
-  if ((threadIdx.x & 63) < 24) W.cof[threadIdx.x & 63] = kTri2WordsDev.w[threadIdx.x & 63];
-  wave_lds_sync();
+// Batched sparse emission: blocks of 64 segments, then of 64 hits, of the series that take the sparse form, each
+// concatenated (bprefix: per-series block prefix, zero blocks for the others); a wavefront's block -> series by binary
+// search.
+__device__ __forceinline__ int series_of_block(const long long* bprefix, int nser, long long B) {
+  int lo = 0, hi = nser;  // bprefix[lo] <= B < bprefix[lo + 1]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (bprefix[mid] <= B)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+__global__ __launch_bounds__(256) void emit2d_ids_batched(const Series2* __restrict__ S,
+                                                          const long long* __restrict__ bprefix, int nser) {
   const long long nblk = bprefix[nser];
-  const long long nw = (long long)gridDim.x * 4;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // wave-uniform: scalar loop state
+  for (long long B = (long long)blockIdx.x * 4 + wv; B < nblk; B += (long long)gridDim.x * 4) {
+    const int lo = series_of_block(bprefix, nser, B);
+    const Grid2 g = S[lo].g;
+    const Out2 o = S[lo].o;
+    emit2d_ids_block(g, B - bprefix[lo], S[lo].masks, S[lo].seg_cnt, S[lo].seg_off, o);
+  }
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(256) void emit2d_sparse_batched(const Series2* __restrict__ S,
+                                                             const long long* __restrict__ bprefix,
+                                                             const unsigned* __restrict__ gbase, int nser,
+                                                             unsigned* status) {
+  __shared__ unsigned cof[24];
+  if (threadIdx.x < 24) cof[threadIdx.x] = kTri2WordsDev.w[threadIdx.x];
+  __syncthreads();
+  const long long nblk = bprefix[nser];
+  // consecutive blocks to one wavefront: it then meets few series, and counts each once
+  const long long waves = (long long)gridDim.x * 4, share = (nblk + waves - 1) / waves;
   unsigned st = 0;
   unsigned long long n_fp64 = 0, n_deg = 0, n_linked = 0;
   int cur = -1;  // series whose counts are being gathered (flushed when the wavefront moves to another)
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // wave-uniform: scalar loop state
-  for (long long B = (long long)blockIdx.x * 4 + wv; B < nblk; B += nw) {
-    int lo = 0, hi = nser;  // bprefix[lo] <= B < bprefix[lo + 1]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (bprefix[mid] <= B)
-        lo = mid;
-      else
-        hi = mid;
-    }
+  const long long first = ((long long)blockIdx.x * 4 + wv) * share;
+  for (long long B = first; B < min(first + share, nblk); ++B) {
+    const int lo = series_of_block(bprefix, nser, B);
     if (lo != cur) {
       if (cur >= 0) sparse_flush_counts(S[cur].cnt, n_fp64, n_deg, n_linked);
       cur = lo;
     }
     const Grid2 g = S[lo].g;
     const Out2 o = S[lo].o;
-    emit2d_sparse_block<WIDE>(g, B - bprefix[lo], S[lo].masks, S[lo].seg_cnt, S[lo].seg_off, o, W, st, n_fp64, n_deg,
-                              n_linked);
+    const long long idx = (long long)gbase[lo] + (B - bprefix[lo]) * 64 + lane_id();
+    if (idx < (long long)gbase[lo + 1])
+      emit2d_hit<WIDE>(g, (unsigned)idx, cof, S[lo].masks, S[lo].seg_cnt, S[lo].seg_off, o, st, n_fp64, n_deg, n_linked);
   }
   if (cur >= 0) sparse_flush_counts(S[cur].cnt, n_fp64, n_deg, n_linked);
   if (st) atomicOr(status, st);
@@ -1797,28 +1793,31 @@ hipError_t launch_emit2d(const Grid2& g, bool wide, int tt, const uint16_t* mask
 }
 
 hipError_t launch_emit2d_sparse(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
-                                const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
-                                hipStream_t s) {
+                                const long long* seg_off, long long n_hits, const Out2& o, unsigned* status,
+                                unsigned long long* cnt, hipStream_t s) {
   const long long nblk = ((long long)(g.t_end - g.t_begin) * g.ny * g.nxt + 63) / 64;
   long long blocks = (nblk + 3) / 4;
   if (blocks > kSparseWaves / 4) blocks = kSparseWaves / 4;
   if (blocks < 1) blocks = 1;
-  if (wide)
-    emit2d_sparse<true><<<(unsigned)blocks, 256, 0, s>>>(g, masks, seg_cnt, seg_off, o, status, cnt);
-  else
-    emit2d_sparse<false><<<(unsigned)blocks, 256, 0, s>>>(g, masks, seg_cnt, seg_off, o, status, cnt);
+  emit2d_ids<<<(unsigned)blocks, 256, 0, s>>>(g, masks, seg_cnt, seg_off, o);
+  long long hb = (n_hits + 255) / 256;
+  if (hb > kSparseWaves / 4) hb = kSparseWaves / 4;
+  if (hb < 1) hb = 1;
+  auto* emit = wide ? emit2d_sparse<true> : emit2d_sparse<false>;
+  emit<<<(unsigned)hb, 256, 0, s>>>(g, masks, seg_cnt, seg_off, n_hits, o, status, cnt);
   return hipGetLastError();
 }
 
-hipError_t launch_emit2d_sparse_batched(const Series2* S, const long long* bprefix, int nser, long long total_blocks,
+hipError_t launch_emit2d_sparse_batched(const Series2* S, const long long* seg_prefix, const long long* hit_prefix,
+                                        const unsigned* gbase, int nser, long long seg_blocks, long long hit_blocks,
                                         bool wide, unsigned* status, hipStream_t s) {
-  long long blocks = (total_blocks + 3) / 4;
-  if (blocks > kSparseWaves / 4) blocks = kSparseWaves / 4;
-  if (blocks < 1) blocks = 1;
-  if (wide)
-    emit2d_sparse_batched<true><<<(unsigned)blocks, 256, 0, s>>>(S, bprefix, nser, status);
-  else
-    emit2d_sparse_batched<false><<<(unsigned)blocks, 256, 0, s>>>(S, bprefix, nser, status);
+  auto grid = [](long long waves) {
+    const long long b = (waves + 3) / 4;
+    return (unsigned)(b > kSparseWaves / 4 ? kSparseWaves / 4 : b < 1 ? 1 : b);
+  };
+  emit2d_ids_batched<<<grid(seg_blocks), 256, 0, s>>>(S, seg_prefix, nser);
+  auto* emit = wide ? emit2d_sparse_batched<true> : emit2d_sparse_batched<false>;
+  emit<<<grid(hit_blocks), 256, 0, s>>>(S, hit_prefix, gbase, nser, status);
   return hipGetLastError();
 }
 

@@ -85,13 +85,15 @@ hipError_t launch_emit2d(const Grid2& g, bool wide, int tt, const uint16_t* mask
                          const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
                          hipStream_t s);
 
-// Sparse emission (one wavefront per non-empty row segment): same outputs as launch_emit2d, for fields with few hits
-// per vertex.  The parents must hold 0xFFFFFFFF on entry; each hit writes its parent (its first smaller partner or
-// an ancestor of it, or itself) and its link slot o.work[i] ((i, i) when absent), united by launch_uf_hook_slots.
+// Sparse emission (ids of the non-empty row segments, then a lane per hit): same outputs as launch_emit2d, for fields
+// with few hits per vertex.  Each hit writes its parent (its first smaller partner or itself) and its link slot
+// o.work[i] ((i, i) when absent), united by launch_uf_hook_slots.
 hipError_t launch_emit2d_sparse(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
-                                const long long* seg_off, const Out2& o, unsigned* status, unsigned long long* cnt,
-                                hipStream_t s);
-hipError_t launch_emit2d_sparse_batched(const Series2* S, const long long* bprefix, int nser, long long total_blocks,
+                                const long long* seg_off, long long n_hits, const Out2& o, unsigned* status,
+                                unsigned long long* cnt, hipStream_t s);
+// Prefixes of the series' blocks of 64 segments and of 64 hits (no blocks: a series in the tiled form).
+hipError_t launch_emit2d_sparse_batched(const Series2* S, const long long* seg_prefix, const long long* hit_prefix,
+                                        const unsigned* gbase, int nser, long long seg_blocks, long long hit_blocks,
                                         bool wide, unsigned* status, hipStream_t s);
 
 hipError_t launch_emit2d_steps(const Grid2& g, bool wide, const uint16_t* masks, const int* seg_cnt,
