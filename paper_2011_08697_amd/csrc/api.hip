@@ -352,14 +352,17 @@ void set_debug(Grid2& g, const ftk_options& o) {
   g.debug_step = (o.debug & FTK_DEBUG_INVARIANT) ? (int)((unsigned)o.debug >> 8) : -1;
 }
 
-// Emission form for a call (or a series of a batch): the sparse one (a wavefront per non-empty row segment) when
-// hits are rare, below one per kSparseVertices vertices, else the tiled one.  Both give identical outputs; the
-// FTK_DEBUG_TILED_EMIT / FTK_DEBUG_SPARSE_EMIT test hooks force either.
-constexpr long long kSparseVertices = 128;
-bool sparse_emission(const Grid2& g, long long n_hits, long long n_vertices) {
+// Emission form for a call (or a series of a batch): the sparse one (ids, then a lane per hit) or the tiled one.  Both
+// give identical outputs; the FTK_DEBUG_TILED_EMIT / FTK_DEBUG_SPARSE_EMIT test hooks force either.  The tiled form pays
+// for its vertices (about 17 ps each more), the sparse one for its hits (58 ps each more) and three launches more
+// (25 us).  Measured, tiled / sparse, us a call: 1024^2 x 24 at 0.03 hits a vertex 749 / 334, at 0.14 981 / 650, at 0.29
+// 1069 / 991, at 0.48 1170 / 1415; 256^2 x 16 at 0.04 148 / 154, at 0.48 186 / 225; 64^2 x 10 at 0.08 101 / 125.
+constexpr long long kSparseFixed = 1500000;  // vertices that pay for the launches
+constexpr long long kSparseHit = 4;          // vertices that pay for a hit
+bool sparse_emission(const Grid2& g, long long n_hits, long long n_vertices, long long fixed) {
   if (g.debug & FTK_DEBUG_SPARSE_EMIT) return true;
   if (g.debug & (FTK_DEBUG_TILED_EMIT | FTK_DEBUG_SMALL_LDS)) return false;  // the hook tests the tiled form
-  return n_hits * kSparseVertices < n_vertices;
+  return n_hits * kSparseHit + fixed < n_vertices;
 }
 
 ftk_status validate_options(const ftk_options& o) {
@@ -625,7 +628,7 @@ ftk_status track2d_core(const float* field, ftk_field_kind kind, int64_t nx, int
   hipError_t he = hipSuccess;
   ph.mark(3);
   if (nh > 0) {
-    const bool sparse = sparse_emission(g, nh, V);
+    const bool sparse = sparse_emission(g, nh, V, kSparseFixed);
     if (sparse) {
       he = launch_emit2d_sparse(g, wide, masks, seg_cnt, seg_off, nh, od, &dctl->status, dctl->cnt, s);
     } else {
@@ -976,9 +979,16 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
   std::vector<char> sparse(nser);
   long long* pre_h = pre_b.data() + nser + 1;
   pre_b[0] = pre_h[0] = 0;
+  long long sparse_vertices = 0;  // the series share the launches of the sparse form
   for (int i = 0; i < nser; ++i) {
     const Grid2& g = ser[i].g;
-    sparse[i] = sparse_emission(g, bases[i + 1] - bases[i], (long long)g.nx * g.ny * g.nt) ? 1 : 0;
+    const long long v = (long long)g.nx * g.ny * g.nt;
+    if (sparse_emission(g, bases[i + 1] - bases[i], v, 0)) sparse_vertices += v;
+  }
+  for (int i = 0; i < nser; ++i) {
+    const Grid2& g = ser[i].g;
+    const long long v = (long long)g.nx * g.ny * g.nt;
+    sparse[i] = sparse_emission(g, bases[i + 1] - bases[i], v, sparse_vertices > kSparseFixed ? 0 : v) ? 1 : 0;
     const int items = pre_e[i + 1] - pre_e[i];
     pre_e[i + 1] = pre_e[i] + (sparse[i] ? 0 : items);
     pre_b[i + 1] = pre_b[i] + (sparse[i] ? ((long long)g.nt * g.ny * g.nxt + 63) / 64 : 0);
