@@ -806,8 +806,8 @@ __device__ __forceinline__ void emit2d_tile(const Grid2& g, int TT, int bx, int 
   unsigned long long n_fp64 = 0, n_deg = 0, n_linked = 0;
 
 
-  // vector field of plane t into gs[par] (field loads from clamped in-grid addresses, all in flight together;
-  // cells outside the grid are zeroed after)
+  // vector field of plane t into gs[par] (field loads from clamped in-grid addresses, all in flight together).  Cells
+  // outside the grid repeat the nearest vertex, so that a one-sided difference is the plain one at its full step.
   auto load_plane = [&](int t, int par) {
     if (!vector) {
       constexpr int NL = (FH * FW + 255) / 256;
@@ -831,28 +831,21 @@ __device__ __forceinline__ void emit2d_tile(const Grid2& g, int TT, int bx, int 
       __syncthreads();
       for (int e = tid; e < GH * GW; e += 256) {
         int ly = e / GW, lx = e - ly * GW;
-        int gx = x0 - 1 + lx, gy = y0 - 1 + ly;
-        float2 v = make_float2(0.0f, 0.0f);
-        if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
-          const float* r = &fs[(ly + 1) * FW + (lx + 1)];
-          v.x = diff3(r[-1], r[0], r[1], gx, nx);
-          v.y = diff3(r[-FW], r[0], r[FW], gy, ny);
-        }
-        gs[par][e] = v;
+        const int gx = min(max(x0 - 1 + lx, 0), nx - 1), gy = min(max(y0 - 1 + ly, 0), ny - 1);
+        const float* r = &fs[(gy - y0 + 2) * FW + (gx - x0 + 2)];
+        gs[par][e] = make_float2(diff3(r[-1], r[0], r[1], gx, nx), diff3(r[-FW], r[0], r[FW], gy, ny));
       }
     } else {
       constexpr int NL = (GH * GW + 255) / 256;
       const float* su = g.f + (long long)fpl(g, t) * 2 * plane;
       const float* sv = su + plane;
       float f0[NL], f1[NL];
-      bool in[NL];
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
         int e = tid + 256 * i;
         asm volatile("" : "+v"(e));
         const int ly = e / GW, lx = e - ly * GW;
         const int gx = x0 - 1 + lx, gy = y0 - 1 + ly;
-        in[i] = e < GH * GW && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
         const long long k = (long long)min(max(gy, 0), ny - 1) * nx + min(max(gx, 0), nx - 1);
         f0[i] = su[k];
         f1[i] = sv[k];
@@ -860,7 +853,7 @@ __device__ __forceinline__ void emit2d_tile(const Grid2& g, int TT, int bx, int 
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
         const int e = tid + 256 * i;
-        if (e < GH * GW) gs[par][e] = in[i] ? make_float2(f0[i], f1[i]) : make_float2(0.0f, 0.0f);
+        if (e < GH * GW) gs[par][e] = make_float2(f0[i], f1[i]);
       }
     }
   };
@@ -1224,10 +1217,11 @@ __device__ __forceinline__ void emit2d_tile(const Grid2& g, int TT, int bx, int 
             if (!(fabsf(qf[i][0]) < 2147483648.0f) || !(fabsf(qf[i][1]) < 2147483648.0f)) wide = true;
           const int gxv = x0 + lxs[i], gyv = y0 + lys[i];
           const float2 xl = G[c - 1], xh = G[c + 1], yl = G[c - GW], yh = G[c + GW];
-          J[i][0] = diff3(xl.x, v.x, xh.x, gxv, nx);
-          J[i][1] = diff3(yl.x, v.x, yh.x, gyv, ny);
-          J[i][2] = diff3(xl.y, v.y, xh.y, gxv, nx);
-          J[i][3] = diff3(yl.y, v.y, yh.y, gyv, ny);
+          const float fx = gxv == 0 || gxv == nx - 1 ? 1.0f : 0.5f, fy = gyv == 0 || gyv == ny - 1 ? 1.0f : 0.5f;
+          J[i][0] = (xh.x - xl.x) * fx;  // diff3: a product with 1 is exact
+          J[i][1] = (yh.x - yl.x) * fy;
+          J[i][2] = (xh.y - xl.y) * fx;
+          J[i][3] = (yh.y - yl.y) * fy;
         }
         hit_record2<WIDE>(g, o, qf, J, wide, vector, ax, y, t, ty, dx1, dy1, dt1, dx2, dy2, dt2, idx, n_fp64,
                           n_deg);
