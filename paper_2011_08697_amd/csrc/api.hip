@@ -14,6 +14,7 @@
 #include "../../include/ftk.h"
 #include "common.h"
 #include "internal.h"
+#include "limits.h"
 
 namespace {
 
@@ -1216,6 +1217,10 @@ static ftk_status tracker_reserve(ftk_tracker* h, long long need, long long keep
 // hits through the last detected step
 static long long tracker_total(const ftk_tracker* h) { return h->total_after.empty() ? 0 : h->total_after.back(); }
 
+// Whether the emission of a 2D step may be queued behind the detection of the next one, before the host has seen its
+// outcome: it reads that step's masks and offsets, not its status or its room, and the offsets must be indices.
+static bool emits_early(const ftk_tracker* h) { return step_fits(tracker_total(h), h->nx * h->ny); }
+
 static Grid2 tracker_grid(ftk_tracker* h, int t_begin, int nt) {
   Grid2 g;
   g.f = h->fring;
@@ -1257,7 +1262,7 @@ static ftk_status tracker_detect(ftk_tracker* h, int p, int nt) {
 static ftk_status tracker_detected(ftk_tracker* h, int p, const Ctl& c) {
   if (c.taken & (ST_NONFINITE | ST_RANGE)) return decode_status(c.taken);
   h->plane_wide[p % 3] = (c.taken & ST_WIDE) ? 1 : 0;
-  if (c.total > 0xFFFFFFFELL) return fail(FTK_ERR_CAPACITY, "%lld punctured simplices exceed 2^32 - 2", c.total);
+  if (c.total > kMaxHits) return fail(FTK_ERR_CAPACITY, "%lld punctured simplices exceed 2^32 - 2", c.total);
   h->total_after.push_back(c.total);
   return tracker_reserve(h, c.total, h->emitted);
 }
@@ -1419,12 +1424,13 @@ extern "C" ftk_status ftk_cp_push(ftk_tracker* h, const float* step) {
   HIP_TRY(hipMemcpyAsync(h->fring + (size_t)(s % 3) * h->step_elems, step, bytes, hipMemcpyDeviceToDevice, h->s));
   ftk_status st = FTK_OK;
   if (h->n == 2) {
-    // the emission of step s - 2 reads the masks and offsets of step s - 1, not its status or its room
+    const bool early = ftk::emits_early(h);
     if (s >= 1) st = ftk::tracker_detect(h, s - 1, ftk::kOpenNt);
-    if (!st && s >= 2) st = ftk::tracker_emit(h, s - 2, ftk::kOpenNt);
+    if (!st && s >= 2 && early) st = ftk::tracker_emit(h, s - 2, ftk::kOpenNt);
     Ctl c;
     if (!st) st = read_ctl(&c, (const Ctl*)h->dctl, h->s);  // also: the caller may reuse `step` on return
     if (!st && s >= 1) st = ftk::tracker_detected(h, s - 1, c);
+    if (!st && s >= 2 && !early) st = ftk::tracker_emit(h, s - 2, ftk::kOpenNt);
   } else {
     if (s >= 1) st = ftk::tracker_detect3(h, s - 1, ftk::kOpenNt);
     if (!st && s >= 2) st = ftk::tracker_emit3(h, s - 2, ftk::kOpenNt);
@@ -1450,10 +1456,12 @@ extern "C" ftk_status ftk_cp_finish(ftk_tracker* h, ftk_cp_result* out) {
   ftk_status st;
   if (h->n == 2) {
     Ctl c;
+    const bool early = ftk::emits_early(h);
     st = ftk::tracker_detect(h, N - 1, N);
-    if (!st) st = ftk::tracker_emit(h, N - 2, N);
+    if (!st && early) st = ftk::tracker_emit(h, N - 2, N);
     if (!st) st = read_ctl(&c, dctl, h->s);
     if (!st) st = ftk::tracker_detected(h, N - 1, c);
+    if (!st && !early) st = ftk::tracker_emit(h, N - 2, N);
     if (!st) st = ftk::tracker_emit(h, N - 1, N);
   } else {
     st = ftk::tracker_detect3(h, N - 1, N);
