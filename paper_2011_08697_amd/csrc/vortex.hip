@@ -271,7 +271,7 @@ __device__ __forceinline__ unsigned vx_partner(const VxGrid& g, const VxTables& 
 // One lane per positive triangle of a word.  The parent is a smaller partner: the one in the tetrahedron below along the
 // lowest axis that the type leaves free, or else one of the same anchor (parents are smaller: a forest, flattened by
 // uf_compress before vx_link).  512 x 128 x 64 x 8: 0.69 ms (one lane per vertex, writing its triangles one by one, 2.57).
-__global__ __launch_bounds__(256) void vx_emit(VxGrid g, long long n_words, const u64* __restrict__ tmask,
+__global__ __launch_bounds__(256) void vx_emit(VxGrid g, long long first, long long n_words, const u64* __restrict__ tmask,
                                                const unsigned short* __restrict__ before, const int* __restrict__ wcnt,
                                                const long long* __restrict__ wbase, long long* __restrict__ tri_id,
                                                float* __restrict__ pos, unsigned* __restrict__ parent) {
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256) void vx_emit(VxGrid g, long long n_words, cons
   __syncthreads();
   VxWave& W = sw[threadIdx.x >> 6];
   VxWord w;
-  const long long k = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long long k = first + (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (!vx_word(g, k, n_words, tmask, before, wcnt, wbase, W, w)) return;
   const long long plane = (long long)g.nx * g.ny * g.nz;
   const bool wide = ((uintptr_t)pos & 15u) == 0;
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(256) void vx_emit(VxGrid g, long long n_words, cons
 // uf_compress most of them agree with the triangle's own and are done; only the others are united.  512 x 128 x 64 x 8,
 // 23 M triangles: 2.3 ms (partners one after another 5.5 ms; groups of the positive triangles of every 4-cube, each
 // member united with its group's first and no forest before, 7.3 ms).
-__global__ __launch_bounds__(256) void vx_link(VxGrid g, long long n_words, const u64* __restrict__ tmask,
+__global__ __launch_bounds__(256) void vx_link(VxGrid g, long long first, long long n_words, const u64* __restrict__ tmask,
                                                const unsigned short* __restrict__ before, const int* __restrict__ wcnt,
                                                const long long* __restrict__ wbase, unsigned* __restrict__ parent) {
   __shared__ VxWave sw[4];
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void vx_link(VxGrid g, long long n_words, cons
   __syncthreads();
   VxWave& W = sw[threadIdx.x >> 6];
   VxWord w;
-  const long long k = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long long k = first + (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (!vx_word(g, k, n_words, tmask, before, wcnt, wbase, W, w)) return;
   for (int i = lane_id(); i < w.n; i += 64) {
     unsigned L, ty;
@@ -420,6 +420,9 @@ __global__ __launch_bounds__(256) void vx_link(VxGrid g, long long n_words, cons
   }
 }
 
+// Words of a launch of the passes over triangles: 64 lanes each, and a launch holds less than 2^32 lanes along x.
+constexpr long long kVxLaunchWords = 1ll << 25;
+
 dim3 vx_grid(const VxGrid& g) {
   return dim3((unsigned)((g.nx + kVxBX - 1) / kVxBX), (unsigned)g.ny, (unsigned)(g.nz * g.nt));
 }
@@ -441,12 +444,21 @@ hipError_t launch_vx_emit(const float* psi, int nx, int ny, int nz, int nt, floa
                           hipStream_t s) {
   const VxGrid g{psi, nx, ny, nz, nt, (nx + 63) / 64, qscale};
   const long long n_words = (long long)nt * nz * ny * g.nwx;
-  const unsigned blocks = (unsigned)((n_words + 3) / 4);
-  vx_emit<<<blocks, 256, 0, s>>>(g, n_words, tmask, before, wcnt, wbase, tri_id, pos, parent);
-  const hipError_t e = launch_uf_compress(parent, n_hits, s);
+  auto each = [&](auto launch) -> hipError_t {
+    for (long long first = 0; first < n_words; first += kVxLaunchWords) {
+      const long long words = n_words - first < kVxLaunchWords ? n_words - first : kVxLaunchWords;
+      launch(first, (unsigned)((words + 3) / 4));
+    }
+    return hipGetLastError();
+  };
+  hipError_t e = each([&](long long first, unsigned blocks) {
+    vx_emit<<<blocks, 256, 0, s>>>(g, first, n_words, tmask, before, wcnt, wbase, tri_id, pos, parent);
+  });
+  if (e == hipSuccess) e = launch_uf_compress(parent, n_hits, s);
   if (e != hipSuccess) return e;
-  vx_link<<<blocks, 256, 0, s>>>(g, n_words, tmask, before, wcnt, wbase, parent);
-  return hipGetLastError();
+  return each([&](long long first, unsigned blocks) {
+    vx_link<<<blocks, 256, 0, s>>>(g, first, n_words, tmask, before, wcnt, wbase, parent);
+  });
 }
 
 }  // namespace ftk
