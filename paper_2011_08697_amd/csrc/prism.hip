@@ -356,52 +356,71 @@ __device__ __forceinline__ void pm_prism_tets(const PmMesh& m, long long T, int 
 
 // From the hits (Alg. 1 pass 2 from the punctured faces' side): each tetrahedron of each prism holding the hit's face
 // has exactly one other punctured side, united with it; any other count is an internal error.  Every tetrahedron with a
-// punctured side is reached from its hits, so this is the all-prism pass below restricted to where it can act.  Eight
-// lanes per hit, one for each tetrahedron of its at most two prisms (two idle): few hits leave the chip idle, so the
-// time is that of one lane's loads (9k hits: 58 -> 31 us).  edge_tri: the (at most two) triangles of each mesh edge,
-// -1 for none.
+// punctured side is reached from its hits, so this is the all-prism pass below restricted to where it can act.  edge_tri:
+// the (at most two) triangles of each mesh edge, -1 for none.
+//
+// SPREAD: eight lanes per hit, one for each tetrahedron of its at most two prisms (two idle).  Few hits leave the chip
+// idle, so the time is that of one lane's loads (9k hits: 58 -> 31 us).  Otherwise one lane per hit, which decodes the hit
+// once for all of them.
+template <bool SPREAD>
 __global__ void pm_unite_hits(PmMesh m, const int* __restrict__ edge_tri, PmHits h,
                               const long long* __restrict__ face_id, long long n_hits,
                               unsigned* __restrict__ parent, unsigned* __restrict__ status) {
-  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x, i = tid >> 3;
-  const int side = (int)(tid >> 2) & 1, k = (int)tid & 3;  // prism and tetrahedron
-  if (i >= n_hits || k == 3) return;
+  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x, i = SPREAD ? tid >> 3 : tid;
+  if (i >= n_hits) return;
   const int t = (int)(face_id[i] / m.S);
   const long long f = face_id[i] - (long long)t * m.S, own = (long long)t * (m.FB * 64) + f;
-  long long T;
-  int pt = t;
-  if (f < m.nf) {  // a mesh triangle: bottom of the prism above it, top of the one below
-    T = f;
-    pt = t - side;
-    if (pt < 0 || pt >= m.nt - 1) return;
-  } else if (f < m.nf + 2 * m.ne) {  // an edge face: the prisms of the edge's triangles
-    T = edge_tri[2 * ((f - m.nf) >> 1) + side];
-    if (T < 0) return;
-  } else {  // an interior face of one prism
-    if (side) return;
-    T = (f - m.nf - 2 * m.ne) >> 1;
-  }
-  long long tet[3][4], p[4];
-  pm_prism_tets(m, T, pt, tet);
-  bool mine = false;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    p[j] = k == 0 ? tet[0][j] : k == 1 ? tet[1][j] : tet[2][j];
-    mine |= p[j] == own;
-  }
-  if (!mine) return;
-  int n = 0;
-  long long other = -1;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (pm_hit(h, p[j])) {
-      ++n;
-      if (p[j] != own) other = p[j];
+  // prism `side` of the face: its triangle and step; false where there is none
+  auto prism = [&](int side, long long& T, int& pt) -> bool {
+    pt = t;
+    if (f < m.nf) {  // a mesh triangle: bottom of the prism above it, top of the one below
+      T = f;
+      pt = t - side;
+      return pt >= 0 && pt < m.nt - 1;
     }
-  if (n == 2)
-    uf_unite_cached(parent, (unsigned)i, (unsigned)pm_index(h, other));
-  else
-    atomicOr(status, ST_INVARIANT);
+    if (f < m.nf + 2 * m.ne) {  // an edge face: the prisms of the edge's triangles
+      T = edge_tri[2 * ((f - m.nf) >> 1) + side];
+      return T >= 0;
+    }
+    T = (f - m.nf - 2 * m.ne) >> 1;  // an interior face of one prism
+    return side == 0;
+  };
+  auto unite = [&](const long long (&p)[4]) {
+    bool mine = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mine |= p[j] == own;
+    if (!mine) return;
+    int n = 0;
+    long long other = -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (pm_hit(h, p[j])) {
+        ++n;
+        if (p[j] != own) other = p[j];
+      }
+    if (n == 2)
+      uf_unite_cached(parent, (unsigned)i, (unsigned)pm_index(h, other));
+    else
+      atomicOr(status, ST_INVARIANT);
+  };
+  long long T, tet[3][4];
+  int pt;
+  if constexpr (SPREAD) {
+    const int side = (int)(tid >> 2) & 1, k = (int)tid & 3;  // prism and tetrahedron
+    if (k == 3 || !prism(side, T, pt)) return;
+    pm_prism_tets(m, T, pt, tet);
+    long long p[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = k == 0 ? tet[0][j] : k == 1 ? tet[1][j] : tet[2][j];
+    unite(p);
+  } else {
+    for (int side = 0; side < 2; ++side) {
+      if (!prism(side, T, pt)) continue;
+      pm_prism_tets(m, T, pt, tet);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) unite(tet[k]);
+    }
+  }
 }
 
 // One lane per (prism, step), for meshes with an edge of more than two triangles (no edge -> triangle table).
@@ -426,6 +445,11 @@ __global__ void pm_unite(PmMesh m, PmHits h, unsigned* __restrict__ parent, unsi
 }
 
 }  // namespace
+
+// Hits up to which the unions take eight lanes a hit.  One lane / eight
+// lanes a hit, us a call on 20k vertices: white noise, 71k hits 150 / 140, 130k 175 / 169, 250k 200 / 211, 1.15M 434 / 544,
+// 12M 3079 / 4328; waves, 23k 180 / 156, 75k 193 / 192, 261k 223 / 287.
+constexpr long long kPmSpreadHits = 1 << 17;
 
 static PmMesh pm_mesh(const float* xy, const int* tri, const int* edge, const int* tri_edge, const float* field,
                       long long nv, long long nf, long long ne, int nt, float qscale) {
@@ -459,8 +483,10 @@ hipError_t launch_pm_emit(const float* xy, const int* tri, const int* edge, cons
   const PmHits h{sc.bits, sc.base};
   const unsigned blocks = (unsigned)((n_hits + 255) / 256);
   pm_emit<<<blocks, 256, 0, s>>>(m, h, n_hits, face_id, pos, parent);
-  if (edge_tri)
-    pm_unite_hits<<<(unsigned)((n_hits + 31) / 32), 256, 0, s>>>(m, edge_tri, h, face_id, n_hits, parent, status);
+  if (edge_tri && n_hits <= kPmSpreadHits)
+    pm_unite_hits<true><<<(unsigned)((n_hits + 31) / 32), 256, 0, s>>>(m, edge_tri, h, face_id, n_hits, parent, status);
+  else if (edge_tri)
+    pm_unite_hits<false><<<blocks, 256, 0, s>>>(m, edge_tri, h, face_id, n_hits, parent, status);
   else if (nt > 1)
     pm_unite<<<dim3((unsigned)((nf + 255) / 256), (unsigned)(nt - 1)), 256, 0, s>>>(m, h, parent, status);
   return hipGetLastError();
