@@ -752,7 +752,8 @@ __global__ void k_place_rulers(const int* __restrict__ list, long long n_rulers,
 }
 
 // Order of the hits between the rulers; *placed += their number.  The entries of a walk are held back until a group of
-// four (32 bytes) is whole: stores of one entry reached memory one by one, 32 bytes each.
+// four (32 bytes) is whole: stores of one entry reached memory one by one, 32 bytes each.  An order array that is not
+// aligned to 16 bytes takes the four as single entries.
 __global__ __launch_bounds__(256) void k_walk_order(const int2* __restrict__ nb, const int* __restrict__ list,
                                                     const unsigned* __restrict__ place, long long n_rulers, int share,
                                                     long long n_hits, long long* __restrict__ order,
@@ -761,6 +762,7 @@ __global__ __launch_bounds__(256) void k_walk_order(const int2* __restrict__ nb,
   const int lane = threadIdx.x & 63;
   long long next = ((long long)blockIdx.x * 4 + (threadIdx.x >> 6)) * share;
   const long long end = min(next + share, n_rulers);
+  const bool wide = ((uintptr_t)order & 15u) == 0;
   bool busy = false;
   int prev = 0, v = 0;
   unsigned p = 0;                  // position of v
@@ -799,13 +801,14 @@ __global__ __launch_bounds__(256) void k_walk_order(const int2* __restrict__ nb,
         busy = false;
       } else {
         if ((p & 3u) == 3u) {
-          if (held == 3) {
+          if (held == 3 && wide) {
             struct alignas(16) Pair {
               long long a, b;
             };
             ((Pair*)(order + p - 3))[0] = Pair{h0, h1};
             ((Pair*)(order + p - 3))[1] = Pair{h2, v};
           } else {
+            if (held > 2) order[p - 3] = h0;
             if (held > 1) order[p - 2] = h1;
             if (held > 0) order[p - 1] = h2;
             order[p] = v;
