@@ -385,20 +385,21 @@ struct Detect2 {
   long long n_hits = 0;
 };
 
-// Detection tile rows and slab depth picked by ftk_autotune_cp2d, per (kind, nx, ny): consulted when the options
-// leave them at 0.  Without an entry the rule of tuned_tiles2 below decides.
+// Detection tile rows and slab depth picked by ftk_autotune_cp2d, per (kind, nx, ny, nt): consulted when the options
+// leave them at 0.  Without an entry the rule of ruled_tiles2 below decides.  The length belongs to the key: a depth that
+// is best for a long series leaves the chip idle on a short one.
 struct TuneKey {
   int kind;
-  long long nx, ny;
-  bool operator==(const TuneKey& k) const { return kind == k.kind && nx == k.nx && ny == k.ny; }
+  long long nx, ny, nt;
+  bool operator==(const TuneKey& k) const { return kind == k.kind && nx == k.nx && ny == k.ny && nt == k.nt; }
 };
 std::mutex g_tune_mu;
 std::vector<std::pair<TuneKey, std::pair<int, int>>> g_tune;
 
-static bool tune_lookup(int kind, long long nx, long long ny, int* ty, int* tt) {
+static bool tune_lookup(const TuneKey& key, int* ty, int* tt) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   for (auto& e : g_tune)
-    if (e.first == TuneKey{kind, nx, ny}) {
+    if (e.first == key) {
       *ty = e.second.first;
       *tt = e.second.second;
       return true;
@@ -406,14 +407,15 @@ static bool tune_lookup(int kind, long long nx, long long ny, int* ty, int* tt) 
   return false;
 }
 
-static void tune_store(int kind, long long nx, long long ny, int ty, int tt) {
+// ty = 0: the rule is the fastest, an earlier entry is dropped
+static void tune_store(const TuneKey& key, int ty, int tt) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  for (auto& e : g_tune)
-    if (e.first == TuneKey{kind, nx, ny}) {
-      e.second = {ty, tt};
-      return;
+  for (size_t i = 0; i < g_tune.size(); ++i)
+    if (g_tune[i].first == key) {
+      g_tune.erase(g_tune.begin() + i);
+      break;
     }
-  g_tune.push_back({TuneKey{kind, nx, ny}, {ty, tt}});
+  if (ty) g_tune.push_back({key, {ty, tt}});
 }
 
 // Steps per slab for a kernel whose work units march `per_step` tiles through time: a slab of tt steps costs about
@@ -449,11 +451,17 @@ static int emit_steps(const Grid2& g) {
   return slab_steps((long long)g.nxt * ((g.ny + kEmitRows - 1) / kEmitRows), g.t_end - g.t_begin, 2, kEmitResident, kEmitSteps);
 }
 
-static void tuned_tiles2(const ftk_options& o, int kind, long long nx, long long ny, int nt, int* ty, int* tt) {
+// The tiling by the rule alone.
+static void ruled_tiles2(long long nx, long long ny, int nt, int* ty, int* tt) {
   const long long waves = ((nx + 63) / 64) * ((ny + kDetectRows - 1) / kDetectRows);
-  int dtt = slab_steps(waves, nt, 1, kDetResident, 16);
-  int dty = waves * ((nt + dtt - 1) / dtt) < 4 * kDetResident ? 8 : 32;
-  tune_lookup(kind, nx, ny, &dty, &dtt);
+  *tt = slab_steps(waves, nt, 1, kDetResident, 16);
+  *ty = waves * ((nt + *tt - 1) / *tt) < 4 * kDetResident ? 8 : 32;
+}
+
+static void tuned_tiles2(const ftk_options& o, int kind, long long nx, long long ny, int nt, int* ty, int* tt) {
+  int dty, dtt;
+  ruled_tiles2(nx, ny, nt, &dty, &dtt);
+  tune_lookup(TuneKey{kind, nx, ny, nt}, &dty, &dtt);
   *ty = o.tile_y ? o.tile_y : dty;
   *tt = o.slab_depth ? o.slab_depth : dtt;
   if (*tt > nt) *tt = nt;
@@ -890,7 +898,7 @@ ftk_status track2d_batched_impl(int nser, const float* const* fields, const int6
       waves += ((nx[i] + 63) / 64) * ((ny[i] + TYD - 1) / TYD);
     }
     int tty, ttt = slab_steps(waves, nt[big], 1, kDetResident, 16);
-    tune_lookup((int)kind, nx[big], ny[big], &tty, &ttt);
+    tune_lookup(TuneKey{(int)kind, nx[big], ny[big], nt[big]}, &tty, &ttt);
     ttd = ttt;
   }
   std::vector<Series2> ser(nser);
@@ -2398,29 +2406,42 @@ extern "C" ftk_status ftk_autotune_cp2d(const float* field, ftk_field_kind kind,
   ph.init(true, s);
   if (!ph.on) return fail(FTK_ERR_HIP, "event creation failed");
   const int rows[3] = {8, 16, 32}, slabs[3] = {8, 16, 32};
+  auto timed = [&](int ty, int tt, float* ms) -> ftk_status {
+    HIP_TRY(ftk::launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));  // warm-up
+    ph.mark(0);
+    for (int r = 0; r < 2; ++r) HIP_TRY(ftk::launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));
+    ph.mark(1);
+    HIP_TRY(hipStreamSynchronize(s));
+    *ms = ph.ms(0, 1);
+    return FTK_OK;
+  };
   int best_ty = 16, best_tt = 16;
   float best = 1e30f;
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {
       const int ty = rows[a], tt = slabs[b] < nt ? slabs[b] : (int)nt;
       if (b > 0 && slabs[b - 1] >= nt) continue;  // same clamped depth as the previous candidate
-      HIP_TRY(ftk::launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));  // warm-up
-      ph.mark(0);
-      for (int r = 0; r < 2; ++r) HIP_TRY(ftk::launch_detect2d(g, ty, tt, masks, seg_cnt, &dctl->status, s));
-      ph.mark(1);
-      HIP_TRY(hipStreamSynchronize(s));
-      const float ms = ph.ms(0, 1);
+      float ms;
+      st = timed(ty, tt, &ms);
+      if (st) return st;
       if (ms < best) {
         best = ms;
         best_ty = ty;
         best_tt = tt;
       }
     }
+  int rule_ty, rule_tt;
+  float rule;
+  ftk::ruled_tiles2(nx, ny, (int)nt, &rule_ty, &rule_tt);
+  st = timed(rule_ty, rule_tt, &rule);
+  if (st) return st;
   Ctl h;
   st = read_ctl(&h, dctl, s);
   if (st) return st;
   if (h.status & ftk::ST_NONFINITE) return decode_status(h.status);
-  ftk::tune_store((int)kind, nx, ny, best_ty, best_tt);
+  // the rule's tiling may be none of the candidates: its slabs are short where there are few tiles (64 x 64 x 10: 9.6 us,
+  // the best candidate 34)
+  ftk::tune_store(ftk::TuneKey{(int)kind, nx, ny, nt}, best < rule ? best_ty : 0, best_tt);
   *tuned = o;
   tuned->tile_y = best_ty;
   tuned->slab_depth = best_tt;
