@@ -110,7 +110,7 @@ typedef struct {
   int64_t cells_linked;     /* (n+1)-simplices holding two punctured sides */
   int64_t fp64_fallbacks;   /* hits whose type needed the FP64 re-evaluation */
   int64_t degenerate_sublocations;
-  int32_t wide_path;        /* 1 if the 128-bit determinant path ran */
+  int32_t wide_path;        /* 1 if the 128-bit determinant path ran (a component of 2^24 or more in 2D, 2^20 in 3D) */
   int32_t reserved;
   float t_detect_ms;        /* with ftk_options.profile: detection kernel (pass 1) */
   float t_scan_ms;          /* prefix sum of the per-segment hit counts */
@@ -392,8 +392,9 @@ typedef struct ftk_mesh ftk_mesh;
 ftk_status ftk_mesh_create(const float* xy, int64_t nv, const int32_t* tri, int64_t nf, ftk_stream_t stream,
                            ftk_mesh** m);
 void ftk_mesh_destroy(ftk_mesh* m);
-/* Tracking on a mesh handle (no host work besides the two count read-backs).  Scratch includes a vertex-major copy
- * of the field (8 nv nt bytes) besides one flag byte per spacetime face. */
+/* Tracking on a mesh handle (no host work besides the two count read-backs).  Scratch: a vertex-major copy of the field
+ * (8 nv nt bytes), the signs of the vertex pairs (16 ne + 8 nv bytes per 64 steps), and 20 bytes per 64 spacetime faces;
+ * then 4 bytes per hit. */
 ftk_status ftk_track_cp_mesh(const ftk_mesh* m, const float* field, int64_t nt, const ftk_options* opt,
                              ftk_stream_t stream, ftk_mesh_result* out);
 /* One-shot form: create, track, destroy. */

@@ -12,7 +12,7 @@ typedef __int128 i128;
 // Device status bits (one word per call).
 enum : unsigned {
   ST_NONFINITE = 1u,  // NaN/Inf in the input
-  ST_WIDE = 2u,       // a quantised component outside the narrow (32-bit or 21-bit) range: rerun the wide path
+  ST_WIDE = 2u,       // a quantised component outside the narrow range (2D 2^24, 3D 2^20): the 128-bit variants run
   ST_RANGE = 4u,      // a quantised component beyond the exact-arithmetic bound
   ST_INVARIANT = 8u,  // a cell with a punctured-side count other than 0 or 2
 };

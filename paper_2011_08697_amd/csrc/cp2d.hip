@@ -5,16 +5,19 @@
 // punctured when the origin is interior to the triangle of its (quantised) vertex vectors, i.e. when the three
 // signed cofactors of (v0 v1 v2 ; 1 1 1) agree (Sec. 4.3, Eq. 2).  Each cofactor is, up to a fixed sign, the 2x2
 // determinant of the two vertex vectors of one edge, so a sign bit is computed once per edge (7 per vertex) and
-// shared by the triangles through LDS.
+// shared by the triangles in registers.
 //
 // Kernels:
 //   detect2d  -- one wavefront per 64 x 8 tile, marching through a slab of steps with the vectors of two planes in
 //                registers: gradient (scalar input), quantisation, the 7 edge signs of every vertex as wave masks and
 //                the 12 triangle tests of every anchor on them; writes a 12-bit puncture mask per vertex and the hit
 //                count of every 64-vertex row segment.
-//   emit2d    -- one wavefront per row segment: prefix sums give each hit its output index (face ids come out
-//                sorted); computes the sublocation (Eq. 2) from the exact cofactors, the Jacobian type (FP32 with
-//                certified FP64 fallback), and the union-find links of the hit's two tetrahedra (Alg. 1 pass 2).
+//   emit2d    -- (dense or small results) one workgroup per 64 x 8 tile, marching through a slab of steps: prefix sums
+//                give each hit its output index (face ids come out sorted), and a lane per hit computes the sublocation
+//                (Eq. 2) from the exact cofactors, the Jacobian type (FP32 with certified FP64 fallback), and the
+//                union-find links of the hit's two tetrahedra (Alg. 1 pass 2), united in LDS within the tile.
+//   emit2d_ids, emit2d_sparse -- (sparse results) the face ids listed from the masks, then a lane per listed hit: the
+//                same records, links into parents and link slots.
 #include "common.h"
 #include "internal.h"
 
@@ -61,8 +64,8 @@ __device__ __forceinline__ int mpl(const Grid2& g, int t) { return g.m_ring ? t 
 // infinitesimals only), so the origin is outside every triangle; with every vector zero each edge determinant takes
 // the perturbation's last, negative term, so the three cofactor signs never agree.
 //
-// Bound: reading the field and writing the masks for sparse fields (8.4 GB at 3.7 TB/s on 4096 x 4096 x 50), VALU issue
-// (about 75 operations a row and step) otherwise.
+// Bound: reading the field and writing the masks for sparse fields (4096 x 4096 x 50: 8.4 GB of them at 3.7 TB/s, 13.4 GB
+// with the halos read again), VALU issue (about 75 operations a row and step) otherwise.
 // ---------------------------------------------------------------------------------------------------------------
 namespace {
 
@@ -1739,7 +1742,7 @@ hipError_t launch_emit2d_steps(const Grid2& g, bool wide, const uint16_t* masks,
 hipError_t launch_detect2d_batched(const Series2* S, const int* prefix, int nser, int total_items, int tt, int kind,
                                    int* counter, unsigned* status, hipStream_t s) {
   int blocks = (total_items + 3) / 4;
-  if (blocks > 1024) blocks = 1024;  // four wavefronts per SIMD
+  if (blocks > 1024) blocks = 1024;  // four wavefronts per SIMD, of which its registers let three be resident
   if (blocks < 1) blocks = 1;
   if (kind != 0)
     detect2d_batched<true><<<blocks, 256, 0, s>>>(S, prefix, nser, tt, counter, status);

@@ -379,7 +379,7 @@ __global__ __launch_bounds__(256) void plan3d(Grid3 g, int steps, int most,
 // tetrahedron, and a triangle word is needed only at the positions that another anchor's tests read.  The anchors left
 // and the positions they need are listed in LDS, and the four wavefronts take the ordinal triangles of plane t, the two
 // halves of the interval ones and the ordinal ones of plane t + 1 of every 64 of them, with dense lanes.  256^3 x 16:
-// 1.04 ms (1.19 when held to four wavefronts per SIMD, whose 128 registers spill); every triangle of every listed tile,
+// 1.04 ms at three wavefronts per SIMD, where a few values spill (1.19 when held to four, where more do); every triangle of every listed tile,
 // in a static order of the runs, took 6.3 ms, and with the facts gathered by the same kernel 9.9 ms.
 // ---------------------------------------------------------------------------------------------------------------
 template <bool WIDE>
@@ -689,7 +689,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Emission + links (hits are sparse: one lane per vertex, 4 row segments per wavefront).
+// Emission + links: the ids listed from the masks, then one lane per hit.
 // ---------------------------------------------------------------------------------------------------------------
 namespace {
 
